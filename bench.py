@@ -46,7 +46,7 @@ PEAK_HBM_GBS = 8000.0
 PEAK_FP8_TFLOPS = 5033.2
 HEADLINE = "square8192_bf16out_t256"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_square8192_gemm.json")
-GEMM_SRC = os.path.join(ROOT, "paper_2601_16294_amd", "csrc", "sfc_gemm.hip")
+GEMM_SRC = os.path.join(ROOT, "paper_2601_16294_amd", "csrc", "sfc_gemm_kernel.h")
 
 
 def log(msg: str) -> None:

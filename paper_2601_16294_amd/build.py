@@ -19,8 +19,11 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libsfcgemm.so")
-SOURCES = ["sfc_order.hip", "sfc_gemm.hip", "sfc_reduce.hip", "sfc_probe.hip", "sfc_model.cpp",
-           "sfcgemm_api.cpp"]
+# longest first
+SOURCES = ["sfc_gemm_256x256_f32.hip", "sfc_gemm_256x256_bf16.hip", "sfc_gemm_256x128.hip", "sfc_gemm_128x256.hip",
+           "sfc_gemm_f8_256x256.hip", "sfc_gemm_f8_128x256.hip", "sfc_gemm_128x128.hip", "sfc_gemm_general.hip",
+           "sfc_gemm.hip", "sfc_order.hip",
+           "sfc_reduce.hip", "sfc_probe.hip", "sfc_model.cpp", "sfcgemm_api.cpp"]
 ARCH = "gfx950"
 
 
@@ -51,7 +54,7 @@ def _compile(src: str) -> str:
 
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    with concurrent.futures.ThreadPoolExecutor(max_workers=4) as ex:
+    with concurrent.futures.ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(_compile, SOURCES))
     tmp = LIB + ".tmp%d" % os.getpid()
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp] + objs

@@ -1,0 +1,10 @@
+#include "sfc_gemm_kernel.h"
+#include "sfc_gemm_variants.h"
+
+namespace sfc {
+
+const void* kernel_128x256(bool ob) {
+  return ob ? kernel_ptr<128, 256, kWaves, 0, true, true>() : kernel_ptr<128, 256, kWaves, 0, false, true>();
+}
+
+}  // namespace sfc

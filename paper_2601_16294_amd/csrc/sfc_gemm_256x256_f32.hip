@@ -1,0 +1,8 @@
+#include "sfc_gemm_kernel.h"
+#include "sfc_gemm_variants.h"
+
+namespace sfc {
+
+const void* kernel_256x256_f32() { return kernel_ptr<256, 256, kWaves, 0, false, true>(); }
+
+}  // namespace sfc
