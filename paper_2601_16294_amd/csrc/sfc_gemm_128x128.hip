@@ -4,11 +4,11 @@
 namespace sfc {
 
 const void* kernel_128x128(bool ob) {
-  return ob ? kernel_ptr<128, 128, kWaves, 0, true, true>() : kernel_ptr<128, 128, kWaves, 0, false, true>();
+  return ob ? kernel_ptr<128, 128, kWaves, 0, true, kLoadRing>() : kernel_ptr<128, 128, kWaves, 0, false, kLoadRing>();
 }
 
 const void* kernel_128x128_deep(bool ob) {
-  return ob ? kernel_ptr<128, 128, kWaves, 0, true, true, 4>() : kernel_ptr<128, 128, kWaves, 0, false, true, 4>();
+  return ob ? kernel_ptr<128, 128, kWaves, 0, true, kLoadRing, 4>() : kernel_ptr<128, 128, kWaves, 0, false, kLoadRing, 4>();
 }
 
 }  // namespace sfc

@@ -4,7 +4,7 @@
 namespace sfc {
 
 const void* kernel_128x256(bool ob) {
-  return ob ? kernel_ptr<128, 256, kWaves, 0, true, true>() : kernel_ptr<128, 256, kWaves, 0, false, true>();
+  return ob ? kernel_ptr<128, 256, kWaves, 0, true, kLoadRing>() : kernel_ptr<128, 256, kWaves, 0, false, kLoadRing>();
 }
 
 }  // namespace sfc

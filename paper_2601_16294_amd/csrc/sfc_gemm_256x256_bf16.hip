@@ -3,6 +3,6 @@
 
 namespace sfc {
 
-const void* kernel_256x256_bf16() { return kernel_ptr<256, 256, kWaves, 0, true, true>(); }
+const void* kernel_256x256_bf16() { return kernel_ptr<256, 256, kWaves, 0, true, kLoadRing>(); }
 
 }  // namespace sfc

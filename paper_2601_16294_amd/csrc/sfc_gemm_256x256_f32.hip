@@ -3,6 +3,6 @@
 
 namespace sfc {
 
-const void* kernel_256x256_f32() { return kernel_ptr<256, 256, kWaves, 0, false, true>(); }
+const void* kernel_256x256_f32() { return kernel_ptr<256, 256, kWaves, 0, false, kLoadRing>(); }
 
 }  // namespace sfc

@@ -4,7 +4,7 @@
 
 namespace sfc {
 
-const void* kernel_256x256_f32();              // two files: each takes minutes to compile
+const void* kernel_256x256_f32();
 const void* kernel_256x256_bf16();
 const void* kernel_256x128(bool ob);
 const void* kernel_128x256(bool ob);
@@ -12,6 +12,7 @@ const void* kernel_128x128(bool ob);
 const void* kernel_128x128_deep(bool ob);      // 4-deep ring
 const void* kernel_f8_256x256(bool ob, int f8);
 const void* kernel_f8_128x256(bool ob, int f8);
-const void* kernel_general(int tile, bool ob);  // any alignment
+const void* kernel_any(int tile, bool ob);       // any alignment, 16-byte loads
+const void* kernel_elements(int tile, bool ob);  // any alignment, element loads
 
 }  // namespace sfc

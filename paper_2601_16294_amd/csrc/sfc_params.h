@@ -38,16 +38,30 @@ struct GemmParams {
 // Curve table of a gm x gn grid into dev_out (gm*gn int32), order = SFC_ORDER_*.
 hipError_t launch_sfc_order(int gm, int gn, int order, int32_t* dev_out, hipStream_t stream);
 
-// Persistent GEMM.  out_bf16 selects the epilogue; vec selects 128-bit loads
-// (needs 16-byte aligned A and B, lda, ldb, K and N multiples of 8).
-// f8 = 0: bf16 operands; f8 = 1 + a + 2b: A and B hold OCP fp8 bytes of format a
-// and b (0 E4M3, 1 E5M2; lda, ldb in elements = bytes); 256x256 only.
-// deep = true: 128x128 blocks on the fast path with a 4-deep ring (one
-// workgroup per CU), for grids of at most one block per CU.
-hipError_t launch_gemm(int tile, bool out_bf16, bool vec, const GemmParams& p, int grid,
-                       hipStream_t stream, int f8 = 0, bool deep = false);
-// Workgroups of the given kernel variant that fit on one CU.
-hipError_t gemm_occupancy(int tile, bool out_bf16, bool vec, int* blocks_per_cu, int f8 = 0, bool deep = false);
+// How a kernel brings its operands into LDS.
+enum Loads {
+  kLoadElements = 0,  // element by element (K or N below 8, or leading dimensions past the 32-bit offsets)
+  kLoadRing = 1,      // 16-byte aligned rows, straight from memory into LDS (vector_loads_ok)
+  kLoadAny = 2,       // any alignment, 16-byte loads through registers (any_loads_ok)
+};
+
+// One compiled GEMM kernel.
+struct Variant {
+  int tile = kT128x128;
+  bool out_bf16 = false;      // epilogue: bf16 C, else fp32
+  int loads = kLoadElements;
+  // 0: bf16 operands; 1 + a + 2b: A and B hold OCP fp8 bytes of format a and b
+  // (0 E4M3, 1 E5M2; lda, ldb in elements = bytes), ring loads only
+  int f8 = 0;
+  // 128x128 blocks on the ring with 4-deep prefetch (one workgroup per CU),
+  // for grids of at most one block per CU
+  bool deep = false;
+};
+
+// Persistent GEMM.
+hipError_t launch_gemm(const Variant& v, const GemmParams& p, int grid, hipStream_t stream);
+// Workgroups of the given kernel that fit on one CU.
+hipError_t gemm_occupancy(const Variant& v, int* blocks_per_cu);
 
 // p[0 .. n) = v (a fill kernel: usable where a memset node is not wanted).
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t stream);

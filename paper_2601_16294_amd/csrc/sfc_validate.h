@@ -128,6 +128,13 @@ inline bool vector_loads_ok(const void* A, int64_t lda, const void* B, int64_t l
          ldb < ((int64_t)1 << 22);
 }
 
+// 16-byte loads at element alignment, staged in registers: a chunk that would
+// run past its row's end starts 8 elements before that end, so rows need 8
+// elements, and byte offsets within a block (256 rows of A, 64 of B) are 32-bit.
+inline bool any_loads_ok(int64_t lda, int64_t ldb, int64_t K, int64_t N) {
+  return K >= 8 && N >= 8 && lda < ((int64_t)1 << 22) && ldb < ((int64_t)1 << 24);
+}
+
 // fp8 (OCP E4M3) operands take the 16-byte load path only: 16-byte aligned
 // rows, and K and N ending on whole 16-element chunks.
 inline bool f8_loads_ok(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t K, int64_t N) {

@@ -47,7 +47,7 @@ struct DeviceState {
   std::map<hipStream_t, StreamMem> streams;
   char* scratch = nullptr;   // this device's copy of `scratch` (see sfc_gemm_noalloc_ex)
   int num_cus = 0;
-  int occupancy[sfc::kNumTiles][2][2][2] = {};               // [tile][bf16 out][vec][fp8 in], 0 = unknown
+  int occupancy[sfc::kNumTiles][2][3][2] = {};               // [tile][bf16 out][loads][fp8 in], 0 = unknown
   int occupancy_deep[2] = {};                                  // 4-deep 128x128 ring, [bf16 out]
 };
 
@@ -169,13 +169,13 @@ int stream_counters(DeviceState& st, hipStream_t stream, int64_t n, int32_t** ou
   return SFC_OK;
 }
 
-int get_occupancy(DeviceState& st, int tile, bool ob, bool vec, int* occ, int f8 = 0, bool deep = false) {
-  int& o = deep ? st.occupancy_deep[ob] : st.occupancy[tile][ob][vec][f8 != 0];
+int get_occupancy(DeviceState& st, const sfc::Variant& v, int* occ) {
+  int& o = v.deep ? st.occupancy_deep[v.out_bf16] : st.occupancy[v.tile][v.out_bf16][v.loads][v.f8 != 0];
   if (o == 0) {
-    int v = 0;
-    hipError_t e = sfc::gemm_occupancy(tile, ob, vec, &v, f8, deep);
+    int n = 0;
+    hipError_t e = sfc::gemm_occupancy(v, &n);
     if (e != hipSuccess) return hip_fail(e, "occupancy query");
-    o = v < 1 ? 1 : v;
+    o = n < 1 ? 1 : n;
   }
   *occ = o;
   return SFC_OK;
@@ -193,7 +193,7 @@ int tile_from_api(int t) {
 
 struct Plan {
   int tile, bm, bn, gm, gn, ce, nk, grid, occ;
-  bool vec;
+  int loads;           // sfc::Loads
   bool deep = false;   // 128x128 blocks with the 4-deep ring (one workgroup per CU)
 };
 
@@ -206,12 +206,12 @@ int make_plan(DeviceState& st, int64_t M, int64_t N, int64_t K, const void* A, i
     // bf16 block and takes the same MFMA time, so the free knobs are chosen by
     // the model for the bf16 problem with the same number of blocks, over the
     // two fp8 block shapes (256x256 first: it keeps a tie).
-    pl->vec = true;
+    pl->loads = sfc::kLoadRing;
     int occ[sfc::kNumTiles];
     for (int t = 0; t < sfc::kNumTiles; ++t) occ[t] = 1;
     static const int kF8Tiles[2] = {sfc::kT256x256, sfc::kT128x256};
     for (int t : kF8Tiles) {
-      rc = get_occupancy(st, t, ob, true, &occ[t], f8);
+      rc = get_occupancy(st, {t, ob, sfc::kLoadRing, f8}, &occ[t]);
       if (rc != SFC_OK) return rc;
     }
     int tile = tile_api == SFC_TILE_AUTO ? -1 : tile_from_api(tile_api);
@@ -234,7 +234,7 @@ int make_plan(DeviceState& st, int64_t M, int64_t N, int64_t K, const void* A, i
     pl->gm = (int)sfc::ceil_div(M, pl->bm);
     pl->gn = (int)sfc::ceil_div(N, pl->bn);
     pl->nk = (int)(K > 0 ? sfc::ceil_div(K, 128) : 0);
-    rc = get_occupancy(st, pl->tile, ob && pl->ce == 1, true, &pl->occ, f8);
+    rc = get_occupancy(st, {pl->tile, ob && pl->ce == 1, sfc::kLoadRing, f8}, &pl->occ);
     if (rc != SFC_OK) return rc;
     const int64_t tasks = (int64_t)pl->gm * pl->gn * pl->ce;
     const int64_t slots = (int64_t)st.num_cus * pl->occ;
@@ -242,12 +242,14 @@ int make_plan(DeviceState& st, int64_t M, int64_t N, int64_t K, const void* A, i
     return SFC_OK;
   }
   // the fast path needs at least one K block per task
-  pl->vec = K > 0 && sfc::vector_loads_ok(A, lda, B, ldb, K, N);
+  pl->loads = K <= 0 ? sfc::kLoadElements
+              : sfc::vector_loads_ok(A, lda, B, ldb, K, N) ? sfc::kLoadRing
+              : sfc::any_loads_ok(lda, ldb, K, N) ? sfc::kLoadAny : sfc::kLoadElements;
   if (tile_api == SFC_TILE_AUTO || ca_layers == SFC_CA_AUTO) {
     // the analytical model evaluates the free knobs (block shape, layers)
     int occ[sfc::kNumTiles];
     for (int t = 0; t < sfc::kNumTiles; ++t) {
-      rc = get_occupancy(st, t, ob && ca_layers == 1, pl->vec, &occ[t]);
+      rc = get_occupancy(st, {t, ob && ca_layers == 1, pl->loads}, &occ[t]);
       if (rc != SFC_OK) return rc;
     }
     const sfc::ModelChoice ch =
@@ -268,8 +270,8 @@ int make_plan(DeviceState& st, int64_t M, int64_t N, int64_t K, const void* A, i
   const bool kernel_bf16 = ob && pl->ce == 1;
   const int64_t tasks = (int64_t)pl->gm * pl->gn * pl->ce;
   // a grid of at most one 128x128 block per CU runs the deep-ring kernel
-  pl->deep = sfc::deep_ring(pl->tile == sfc::kT128x128, pl->vec, 0, tasks, st.num_cus);
-  rc = get_occupancy(st, pl->tile, kernel_bf16, pl->vec, &pl->occ, 0, pl->deep);
+  pl->deep = sfc::deep_ring(pl->tile == sfc::kT128x128, pl->loads == sfc::kLoadRing, 0, tasks, st.num_cus);
+  rc = get_occupancy(st, {pl->tile, kernel_bf16, pl->loads, 0, pl->deep}, &pl->occ);
   if (rc != SFC_OK) return rc;
   int64_t slots = (int64_t)st.num_cus * pl->occ;
   pl->grid = (int)(tasks < slots ? tasks : slots);
@@ -292,13 +294,13 @@ struct Split {
 int plan_tail_split(DeviceState& st, const Plan& pl, int64_t M, int64_t N, int64_t K, const void* A,
                     int64_t lda, const void* B, int64_t ldb, bool ob, Split* sp) {
   sp->on = false;
-  if (pl.ce != 1 || !pl.vec) return SFC_OK;
+  if (pl.ce != 1 || pl.loads != sfc::kLoadRing) return SFC_OK;
   int half;
   if (pl.tile == sfc::kT256x256) half = sfc::kT128x256;
   else if (pl.tile == sfc::kT256x128) half = sfc::kT128x128;
   else return SFC_OK;
   int occ2 = 1;
-  int rc = get_occupancy(st, half, ob, true, &occ2);
+  int rc = get_occupancy(st, {half, ob, sfc::kLoadRing}, &occ2);
   if (rc != SFC_OK) return rc;
   const int64_t half_rows = sfc::ceil_div(M, sfc::tile_bm(half));
   const int w = sfc::strip_columns(pl.gm, pl.gn, (int64_t)st.num_cus * pl.occ, half_rows,
@@ -314,8 +316,8 @@ int plan_tail_split(DeviceState& st, const Plan& pl, int64_t M, int64_t N, int64
   q.ce = 1;
   q.nk = pl.nk;
   q.occ = occ2;
-  q.vec = sfc::vector_loads_ok(A, lda, static_cast<const uint16_t*>(B) + n1, ldb, K, N - n1);
-  if (!q.vec) return SFC_OK;
+  q.loads = sfc::kLoadRing;
+  if (!sfc::vector_loads_ok(A, lda, static_cast<const uint16_t*>(B) + n1, ldb, K, N - n1)) return SFC_OK;
   q.grid = (int)((int64_t)q.gm * q.gn);
   sp->w = w;
   sp->on = true;
@@ -351,7 +353,7 @@ int launch_plan(const Plan& pl, const int32_t* table, int64_t M, int64_t N, int6
   p.counters = fu.counters;
   p.C = fu.C;
   p.ldc = fu.ldc;
-  hipError_t e = sfc::launch_gemm(pl.tile, out_bf16, pl.vec, p, pl.grid, stream, f8, pl.deep);
+  hipError_t e = sfc::launch_gemm({pl.tile, out_bf16, pl.loads, f8, pl.deep}, p, pl.grid, stream);
   if (e != hipSuccess) return hip_fail(e, "GEMM launch");
   return SFC_OK;
 }

@@ -1,0 +1,69 @@
+"""The any-alignment path (16-byte loads at element alignment, staged in
+registers): the ends of rows, where a chunk is loaded early and shifted, the
+last rows, the last K block of a layer, and the limits where the path begins and
+ends.  Integer operands make every sum exact in fp32 (|sum| <= 16 K < 2^24), so
+results are compared bit for bit; padding holds NaN, so an element used from
+outside a row shows."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import bf16 as obf16
+from paper_2601_16294_amd.inputs import draw
+from gpu_util import run_gemm, to_host, upload, sg
+
+pytestmark = pytest.mark.gpu
+
+TILES = ["128x128", "256x128", "128x256", "256x256"]
+
+
+def check(M, N, K, tile, c, out, lda, ldb, ldc, seed):
+    A = draw(M, K, ("int", -4, 4), seed, lda)
+    B = draw(K, N, ("int", -4, 4), seed + 1, ldb)
+    C = run_gemm(A, B, M, N, K, out=out, ldc=ldc, ca_layers=c, tile=tile)
+    want = (obf16.bf16_to_f64(A[:, :K]).astype(np.int64) @ obf16.bf16_to_f64(B[:, :N]).astype(np.int64))
+    want = want.astype(np.float32)
+    if out == "bf16":
+        want = obf16.bf16_to_f64(obf16.f32_to_bf16_rne(want))
+    assert np.array_equal(C[:, :N], want.astype(np.float64)), (M, N, K, tile, c, out)
+    assert np.isnan(C[:, N:]).all()
+
+
+# every remainder of K and of N modulo the 8-element chunk, around the 64-deep
+# block and the 128/256-wide tile
+@pytest.mark.parametrize("r", range(8))
+@pytest.mark.parametrize("tile", TILES)
+def test_row_end_remainders(r, tile):
+    check(129, 256 + r, 64 + r, tile, 1, "f32", 64 + r + 1, 256 + r + 3, 256 + r + 1, 2000 + r)
+    check(131, 127 + r, 121 + r, tile, 2, "bf16", 121 + r, 127 + r, 127 + r, 2100 + r)
+
+
+# the smallest sizes of the path, sizes below it (element loads), one row, one
+# block column with fewer than 8 columns in the last chunk
+@pytest.mark.parametrize("M,N,K", [(1, 8, 8), (3, 9, 15), (1, 1001, 77), (257, 8, 63), (65, 265, 9), (5, 7, 64),
+                                   (64, 64, 7), (300, 513, 129)])
+@pytest.mark.parametrize("tile", TILES)
+def test_small_and_edge_sizes(M, N, K, tile):
+    check(M, N, K, tile, 1, "f32", K + 1, N + 1, N, 2200 + M + N + K)
+    check(M, N, K, tile, 1, "bf16", K, N, N + 5, 2300 + M + N + K)
+
+
+# layers whose last blocks are whole and whose last layer runs past K
+@pytest.mark.parametrize("c", [1, 2, 3, 7])
+def test_layers(c):
+    for K in (447, 448 + 1, 65):
+        check(140, 261, K, "auto", c, "f32", K, 261, 261, 2400 + K + c)
+
+
+def test_leading_dimension_limit():
+    # 2^22 - 1 is the last leading dimension of A with 32-bit offsets in a block
+    for lda in ((1 << 22) - 1, 1 << 22):
+        M, N, K = 3, 40, 72
+        A = draw(M, K, ("int", -4, 4), 2500)
+        B = draw(K, N, ("int", -4, 4), 2501)
+        big = torch.full((M, lda), float("nan"), dtype=torch.bfloat16, device="cuda")
+        big[:, :K] = upload(A)
+        C = torch.empty((M, N), dtype=torch.float32, device="cuda")
+        sg().sfc_gemm_ex(big[:, :K], upload(B), C)
+        want = obf16.bf16_to_f64(A).astype(np.int64) @ obf16.bf16_to_f64(B).astype(np.int64)
+        assert np.array_equal(to_host(C), want.astype(np.float64)), lda
