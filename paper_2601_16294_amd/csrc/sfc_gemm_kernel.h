@@ -28,9 +28,10 @@
 //     fragment read of the next step and one load operation for the blocks
 //     ahead, and small pieces of the scalar bookkeeping (a wave issues one
 //     instruction every 4 cycles, a 16x16x32 MFMA takes 16);
-//   * any alignment: 16-byte loads at element alignment through registers, two
-//     64-deep LDS buffers (element by element only where a row has fewer than 8
-//     elements or byte offsets pass 32 bits);
+//   * any alignment: the same ring (loads into LDS take any element alignment);
+//     where K or N is no multiple of 8 the last K block goes through registers
+//     (element by element only where a row has fewer than 8 elements or byte
+//     offsets pass 32 bits);
 //   * the MFMA B operand is read from [k][n] with the transposing LDS read
 //     (ds_read_b64_tr_b16); 16-byte chunks are XOR-swizzled so that the
 //     fragment reads and the staging writes are free of bank conflicts on the
@@ -1044,36 +1045,30 @@ __device__ __forceinline__ void main_loop_staged(const GemmParams& p, uint16_t* 
   }
 }
 
-// ---- main loop, any alignment: 16-byte loads staged in registers ----------------------------
-// Rows that do not start 16-byte aligned cannot go straight into LDS, so a block
-// passes through registers: each thread loads 16-byte chunks at element
-// alignment, a block ahead, and writes them into the other of two LDS buffers.
-// The schedule is the ring's in small: the first 32-deep step of block b runs
-// its MFMAs beside the LDS writes of block b+1 and the loads of block b+2, and
-// reads the second step's fragments; the second step meets the block's barrier
-// after its first MFMAs and reads the first fragments of block b+1.
+// ---- any alignment: the ring, and a last K block through registers ---------------------------
+// The hardware runs with unaligned access on (the mode the compiler's own loads of
+// packed types rely on), and in it a 16-byte load into LDS takes any 2-byte aligned
+// address, so rows of any alignment run on the ring above.  Only the ends of rows
+// differ: the chunk that holds the last K % 8 elements of a row of A, or the last
+// N % 8 of a row of B, runs into the next row, and in the matrix's last row past
+// its end.  (The descriptor's range cannot cut it there: it is checked per dword of
+// the chunk, and a valid last element may share its dword with the first byte past
+// the end.)  Every K block but the last is followed by another row of B and by
+// more elements of each row of A, so its chunks stay inside the matrices; what a
+// chunk of B brings from past N feeds only columns that are not stored.  So when K
+// or N is no multiple of 8 the ring takes the blocks before the last, and the last
+// block goes through registers (any_tail): a chunk that would run past its row's
+// end starts 8 elements before that end and is shifted down, rows past the end
+// re-read the last row, B rows past K are written as zeros.  Needs K, N >= 8
+// (any_loads_ok).
 //
-// No load leaves the matrix: a chunk that would run past its row's end (K for
-// A, N for B) starts 8 elements before that end instead and is shifted down
-// when it is written, rows past the end re-read the last row.  Rows of B past K
-// are written as zeros (as are A's columns past K, by the shift), so that
-// neither operand's garbage reaches a product; rows of A past M and columns of
-// B past N only feed outputs that are not stored.  Needs K, N >= 8 and 32-bit
-// byte offsets within a block (any_loads_ok).
-//
-// Bound: the K loop is MFMA work beside LDS traffic, as the ring's; a block's
-// loads have about one block's time (2000+ clocks for 256x256) to arrive.
-// Against the element loads this replaces (16-bit loads, 64-bit addresses and
-// selects per element), same box, bits identical: 3001x5003x2047 fp32 out 516 us
-// -> 97 us, 91 us with 16-byte stores at element alignment (store_tile_any);
-// 333x517x421 bf16 out 41.1 us -> 13.7 us -> 11.9 us.
+// Bound: as the ring's; an unaligned row of a block touches one more 128-byte line,
+// and the last block's load latency is exposed once per task.  Against a K loop
+// that brought every block through registers (16-byte loads a block ahead, LDS
+// writes beside the MFMAs), same box, bits identical: 3001x5003x2047 fp32 out
+// 91 -> 72 us (aligned 3000x5000x2048: 70), 5999x5001x4097 fp32 out 262 us; element
+// loads took 514 us on the first.
 struct __attribute__((packed, aligned(2))) Chunk16 { u32x4 v; };
-
-// f<0>(), f<1>(), .., f<N-1>() as straight-line code.
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  [&]<int... i>(std::integer_sequence<int, i...>) { (f.template operator()<i>(), ...); }(std::make_integer_sequence<int, N>{});
-}
 
 // The 8 elements of v moved down by sh (0 .. 7), zeros behind; all zeros for sh >= 8.
 __device__ __forceinline__ u32x4 shift_chunk(u32x4 v, int sh) {
@@ -1091,188 +1086,56 @@ __device__ __forceinline__ u32x4 shift_chunk(u32x4 v, int sh) {
   return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
 }
 
-// Per-thread state of the loads and writes of one task.
+// acc += block kt, the last of K (1 to 64 rows of B), through registers.  The LDS
+// is free on entry and on return.
 template <int BM, int BN, int NW>
-struct AnyLanes {
+__device__ __forceinline__ void any_tail(const GemmParams& p, uint16_t* smem, int64_t m0, int64_t n0, int kt, int tid,
+                                         Acc<BM, BN, NW, 0>& acc) {
   using T = Tile<BM, BN, NW, 0>;
-  static constexpr int CPR = BN / 8;                 // 16-byte chunks per row of a B block
-  static constexpr int A_RSTEP = T::THREADS / 8;     // rows between a thread's A chunks
-  static constexpr int B_RSTEP = T::THREADS / CPR;   // rows between a thread's B chunks
-  uint32_t a_row[T::A_CH];   // byte offset of each A chunk's row from the block's first row
-  uint32_t b_col;            // byte offset of the thread's first B chunk from the block's first row
-  int a_k;                   // K element (within a block) of the thread's A chunks
-  int b_row;                 // first B row of the thread
-  int b_sh;                  // shift of the thread's B chunks (last block column)
-  u32x4 a[T::A_CH], b[T::B_CH];
-};
-
-template <int BM, int BN, int NW>
-struct AnyTask {
-  const char* A;        // row m0 of A
-  const char* B;        // column n0 of B
-  int64_t lda2, ldb2;   // bytes per row
-  int K;
-  int kt1;              // end of the task's K blocks
-  bool edge_n;          // the block column runs past N
-};
-
-template <int BM, int BN, int NW, int C>
-__device__ __forceinline__ void any_load_a(const AnyTask<BM, BN, NW>& t, AnyLanes<BM, BN, NW>& L, uint32_t koff) {
-  L.a[C] = reinterpret_cast<const Chunk16*>(t.A + (L.a_row[C] + koff))->v;
-}
-// rows past K re-read row K-1: the row offset saturates (last_row: byte offset
-// of the block's last row that is loaded)
-template <int BM, int BN, int NW, int C>
-__device__ __forceinline__ void any_load_b(const AnyTask<BM, BN, NW>& t, AnyLanes<BM, BN, NW>& L, const char* base,
-                                           uint32_t row_step, uint32_t last) {
-  uint32_t off = L.b_col + (uint32_t)C * row_step;
-  off = off < last ? off : last;
-  L.b[C] = reinterpret_cast<const Chunk16*>(base + off)->v;
-}
-
-template <int BM, int BN, int NW>
-__device__ __forceinline__ void main_loop_any(const GemmParams& p, uint16_t* smem, int64_t m0, int64_t n0, int kt0,
-                                              int kt1, int tid, Acc<BM, BN, NW, 0>& acc) {
-  using T = Tile<BM, BN, NW, 0>;
-  using AL = AnyLanes<BM, BN, NW>;
-  constexpr int G = T::FM * T::FN;
-  constexpr int NCH = T::A_CH + T::B_CH;             // chunks per thread and block
-  constexpr int NR = T::FM + T::FN;                  // fragments per step
-  constexpr int G0 = 2;                              // MFMAs of the second step ahead of the barrier
-  constexpr int BUF = T::A_ELEMS + T::B_ELEMS;
+  constexpr int CPR = BN / 8;                 // 16-byte chunks per row of a B block
+  constexpr int A_RSTEP = T::THREADS / 8;     // rows between a thread's A chunks
+  constexpr int B_RSTEP = T::THREADS / CPR;   // rows between a thread's B chunks
   const int lane = tid & 63, wave = tid >> 6;
   const int wm = wave / T::WGN, wn = wave % T::WGN;
-
-  AnyTask<BM, BN, NW> t;
-  t.lda2 = p.lda * 2;
-  t.ldb2 = p.ldb * 2;
-  t.A = reinterpret_cast<const char*>(p.A) + m0 * t.lda2;
-  t.B = reinterpret_cast<const char*>(p.B) + n0 * 2;
-  t.K = (int)p.K;
-  t.kt1 = kt1;
-  t.edge_n = n0 + BN > p.N;
-  const int nk_rows = (int)(p.M - m0 < BM ? p.M - m0 : BM);
+  const int64_t k0 = (int64_t)kt * kBK;
+  const int m_left = (int)(p.M - m0 < BM ? p.M - m0 : BM);
   const int n_left = (int)(p.N - n0 < BN ? p.N - n0 : BN);
-
-  AL L;
-  L.a_k = (tid & 7) * 8;
+  const int k_left = (int)(p.K - k0);         // 1 .. 64
+  const int a_row = tid >> 3, a_k = (tid & 7) * 8;
+  const int b_row = tid / CPR, col = (tid % CPR) * 8;
+  // the last chunks that fit; the one of B may start in the block column to the
+  // left (n0 >= 8 there), the one of A in the block before
+  const int ak = a_k < k_left - 8 ? a_k : k_left - 8;
+  const int bc = col < n_left - 8 ? col : n_left - 8;
+  const uint16_t* A = p.A + m0 * p.lda + k0 + ak;
+  const uint16_t* B = p.B + k0 * p.ldb + n0 + bc;
+  u32x4 ra[T::A_CH], rb[T::B_CH];
 #pragma unroll
   for (int i = 0; i < T::A_CH; ++i) {
-    const int row = (tid >> 3) + AL::A_RSTEP * i;
-    L.a_row[i] = (uint32_t)((row < nk_rows ? row : nk_rows - 1) * t.lda2);
+    const int row = a_row + A_RSTEP * i;
+    ra[i] = reinterpret_cast<const Chunk16*>(A + (row < m_left ? row : m_left - 1) * p.lda)->v;
   }
-  L.b_row = tid / AL::CPR;
-  const int col = (tid % AL::CPR) * 8;
-  // the last chunk that fits starts 8 columns before N; it may lie in the
-  // block column to the left (n0 >= 8 there) when fewer than 8 columns are left
-  const int bc = col < n_left - 8 ? col : n_left - 8;
-  L.b_sh = col - bc;
-  // may be negative only through bc; the row part is added in 64 bits below
-  const int64_t col_bytes = (int64_t)bc * 2;
-  L.b_col = (uint32_t)(L.b_row * t.ldb2);
-
-  uint32_t koff = 0, b_last = 0;
-  const uint32_t b_step = (uint32_t)(AL::B_RSTEP * t.ldb2);
-  const char* b_base = nullptr;
-  const int kbytes_max = (t.K - 8) * 2;
-  // addresses of block kt
-  auto addr = [&](int kt) {
-    const int kb = (kt * kBK + L.a_k) * 2;
-    koff = (uint32_t)(kb < kbytes_max ? kb : kbytes_max);
-    const int64_t k0 = (int64_t)kt * kBK;
-    const int rows = (int)(t.K - k0 < kBK ? t.K - k0 : kBK);
-    b_last = (uint32_t)((rows - 1) * t.ldb2);
-    b_base = t.B + k0 * t.ldb2;
-  };
-  auto load_one = [&]<int c>() {
-    if constexpr (c < T::A_CH) {
-      any_load_a<BM, BN, NW, c>(t, L, koff);
-    } else {
-      any_load_b<BM, BN, NW, c - T::A_CH>(t, L, b_base + col_bytes, b_step, b_last);
-    }
-  };
-  // write chunk c of block kt into buffer `buf`; fix: the block runs past K or
-  // past N, and its chunks are shifted or cleared first
-  auto write_one = [&]<int c>(uint16_t* buf, int kt, bool fix) {
-    if constexpr (c < T::A_CH) {
-      u32x4 v = L.a[c];
-      if (fix) {
-        const int k = kt * kBK + L.a_k;
-        v = shift_chunk(v, k <= t.K - 8 ? 0 : k - (t.K - 8));
-      }
-      *reinterpret_cast<u32x4*>(buf + a_off((tid >> 3) + AL::A_RSTEP * c, tid & 7)) = v;
-    } else {
-      constexpr int i = c - T::A_CH;
-      const int row = L.b_row + AL::B_RSTEP * i;
-      u32x4 v = L.b[i];
-      if (fix) {
-        v = shift_chunk(v, L.b_sh);
-        if (kt * kBK + row >= t.K) v = u32x4{0u, 0u, 0u, 0u};
-      }
-      *reinterpret_cast<u32x4*>(buf + T::A_ELEMS + b_off<BN>(row, col)) = v;
-    }
-  };
-  auto needs_fix = [&](int kt) { return t.edge_n || (kt + 1) * kBK > t.K; };
-
-  // fragment r of step ks of the block in `buf`: A0, B0 .. B(FN-1), A1 ..
-  auto read_one = [&]<int r>(const uint16_t* buf, int ks, Frags<BM, BN, NW, 0>& f) {
-    if constexpr (r == 0 || r > T::FN) {
-      constexpr int i = r == 0 ? 0 : r - T::FN;
-      f.a[i] = *reinterpret_cast<const bf16x8*>(buf + a_frag_off(wm * T::WTM, lane, ks) + i * 16 * kBK);
-    } else {
-      f.b[r - 1] = read_b_pair(buf + T::A_ELEMS + b_frag_off<BN>(wn * T::WTN, lane, 32 * ks, r - 1), 4 * BN);
-    }
-  };
-
-  // block kt0 into buffer 0, block kt0+1 into the registers
-  addr(kt0);
-  static_for<NCH>(load_one);
-  {
-    const bool fix = needs_fix(kt0);
-    static_for<NCH>([&]<int c>() { write_one.template operator()<c>(smem, kt0, fix); });
+#pragma unroll
+  for (int i = 0; i < T::B_CH; ++i) {
+    const int row = b_row + B_RSTEP * i;
+    rb[i] = reinterpret_cast<const Chunk16*>(B + (row < k_left ? row : k_left - 1) * p.ldb)->v;
   }
-  addr(kt0 + 1 < kt1 ? kt0 + 1 : kt0);
-  static_for<NCH>(load_one);
+  uint16_t* Bs = smem + T::A_ELEMS;
+#pragma unroll
+  for (int i = 0; i < T::A_CH; ++i)
+    *reinterpret_cast<u32x4*>(smem + a_off(a_row + A_RSTEP * i, tid & 7)) = shift_chunk(ra[i], a_k - ak);
+#pragma unroll
+  for (int i = 0; i < T::B_CH; ++i) {
+    const int row = b_row + B_RSTEP * i;
+    *reinterpret_cast<u32x4*>(Bs + b_off<BN>(row, col)) = shift_chunk(rb[i], row < k_left ? col - bc : 8);
+  }
   __syncthreads();
-  Frags<BM, BN, NW, 0> f0, f1;
-  static_for<NR>([&]<int r>() { read_one.template operator()<r>(smem, 0, f0); });
-
-  for (int kt = kt0; kt < kt1; ++kt) {
-    uint16_t* cur = smem + ((kt - kt0) & 1) * BUF;
-    uint16_t* oth = smem + (((kt - kt0) & 1) ^ 1) * BUF;
-    const bool fix = needs_fix(kt + 1);
-    // past the task's last block the loads repeat it (in bounds, unused)
-    addr(kt + 2 < kt1 ? kt + 2 : kt1 - 1);
-    // step 1: MFMAs of f0, reads of f1, block kt+1 into the other buffer and
-    // the loads of block kt+2 into the registers this frees
-    static_for<G>([&]<int g>() {
-      constexpr int i = g / T::FN, j = g % T::FN;
-      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f0.b[j], f0.a[i], acc[i][j], 0, 0, 0);
-      static_for<NR>([&]<int r>() {
-        if constexpr (r * G / NR == g) read_one.template operator()<r>(cur, 1, f1);
-      });
-      static_for<NCH>([&]<int c>() {
-        if constexpr (c * G / NCH == g) {
-          write_one.template operator()<c>(oth, kt + 1, fix);
-          load_one.template operator()<c>();
-        }
-      });
-      __builtin_amdgcn_sched_barrier(0);
-    });
-    // step 2: MFMAs of f1, the barrier, reads of block kt+1's first fragments
-    static_for<G>([&]<int g>() {
-      constexpr int i = g / T::FN, j = g % T::FN;
-      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f1.b[j], f1.a[i], acc[i][j], 0, 0, 0);
-      // at the barrier this wave's writes of block kt+1 and reads of block kt
-      // are done (the register loads in flight are not waited for)
-      if constexpr (g == G0) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-      static_for<NR>([&]<int r>() {
-        if constexpr (G0 + r * (G - G0) / NR == g) read_one.template operator()<r>(oth, 0, f0);
-      });
-      __builtin_amdgcn_sched_barrier(0);
-    });
+  for (int ks = 0; ks * 32 < k_left; ++ks) {
+    Frags<BM, BN, NW, 0> f;
+    load_frags<BM, BN, NW, 0>(smem, Bs, wm, wn, lane, ks, 32 * ks, f);
+    mma_step<BM, BN, NW, 0>(f, acc);
   }
-  __syncthreads();   // every wave is done with the buffers before the next task writes them
+  __syncthreads();
 }
 
 // ---- epilogue ---------------------------------------------------------------------------------
@@ -1748,9 +1611,9 @@ template <int BM, int BN, int NW, int F8, bool OUT_BF16, int LOADS, int D = defa
 __global__ __launch_bounds__(NW * 64, 1) void sfc_gemm_kernel(GemmParams p) {
   using T = Tile<BM, BN, NW, F8>;
   static_assert(T::A_CH >= 1 && T::B_CH >= 1, "tile too small for the workgroup");
-  constexpr bool VEC = LOADS == kLoadRing;
-  static_assert(!F8 || VEC, "fp8 operands take the fast path only");
-  // fast path: the rings of A block and B stage slots; general path: two 64-deep blocks
+  constexpr bool VEC = LOADS != kLoadElements;
+  static_assert(!F8 || LOADS == kLoadRing, "fp8 operands take aligned rows only");
+  // the rings of A block and B stage slots; element loads: two 64-deep blocks
   constexpr int kSmem = VEC ? Ring<BM, BN, NW, F8, D>::ELEMS : 2 * (T::A_ELEMS + T::B_ELEMS);
   __shared__ __attribute__((aligned(16))) uint16_t smem[kSmem];
 
@@ -1807,7 +1670,10 @@ __global__ __launch_bounds__(NW * 64, 1) void sfc_gemm_kernel(GemmParams p) {
         else acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
 
-    if (kt0 < kt1) {
+    // any alignment: the last K block may go through registers (any_tail)
+    const bool tail = LOADS == kLoadAny && kt1 == p.nk && ((p.K | p.N) & 7) != 0;
+    const int ktr = tail ? kt1 - 1 : kt1;        // end of the ring's blocks
+    if (kt0 < ktr) {
       if constexpr (VEC) {
         constexpr int ESZ = F8 ? 1 : 2;          // bytes per element
         constexpr int SK = stage_k<F8>();
@@ -1824,7 +1690,7 @@ __global__ __launch_bounds__(NW * 64, 1) void sfc_gemm_kernel(GemmParams p) {
           // rows of B from the task's first stage to the end of its layer's K
           // range (row K for the last layer): the stages that the ring loads
           // ahead past that point get empty ranges and fetch nothing
-          const int64_t k_end = (int64_t)kt1 * block_k<F8>() < p.K ? (int64_t)kt1 * block_k<F8>() : p.K;
+          const int64_t k_end = (int64_t)ktr * block_k<F8>() < p.K ? (int64_t)ktr * block_k<F8>() : p.K;
           const int b_rows = (int)(k_end - k0);
           ra.x_part = b_rows / SK;
           ra.lim_part = (uint32_t)((b_rows % SK) * (int)(p.ldb * ESZ) + kBias);
@@ -1834,14 +1700,15 @@ __global__ __launch_bounds__(NW * 64, 1) void sfc_gemm_kernel(GemmParams p) {
         // K elements of the task's last block that lie before K (a full
         // block unless the block runs past K), in 32 bits: the per-lane K-mask
         // compares then stay single registers
-        const int64_t kin64 = p.K - (int64_t)(kt1 - 1) * block_k<F8>();
+        const int64_t kin64 = p.K - (int64_t)(ktr - 1) * block_k<F8>();
         const int kin_last = kin64 < block_k<F8>() ? (int)kin64 : block_k<F8>();
-        main_loop_ring<BM, BN, NW, F8, D>(ra, kt1 - kt0, kin_last, ro, L, lane_t, acc);
-      } else if constexpr (LOADS == kLoadAny) {
-        main_loop_any<BM, BN, NW>(p, smem, m0, n0, kt0, kt1, tid, acc);
+        main_loop_ring<BM, BN, NW, F8, D>(ra, ktr - kt0, kin_last, ro, L, lane_t, acc);
       } else if constexpr (!F8) {
-        main_loop_staged<BM, BN, NW, F8>(p, smem, m0, n0, kt0, kt1, tid, acc);
+        main_loop_staged<BM, BN, NW, F8>(p, smem, m0, n0, kt0, ktr, tid, acc);
       }
+    }
+    if constexpr (LOADS == kLoadAny) {
+      if (tail) any_tail<BM, BN, NW>(p, smem, m0, n0, kt1 - 1, tid, acc);
     }
 
     const int64_t lstride = p.out_layer_stride * layer;
@@ -1849,8 +1716,8 @@ __global__ __launch_bounds__(NW * 64, 1) void sfc_gemm_kernel(GemmParams p) {
     // layer copies that this launch reduces itself are stored coherently
     constexpr bool kFusable = !OUT_BF16 && F8 == 0;
     const bool fused = kFusable && p.counters != nullptr;
-    if (VEC && Staging<BM, BN, NW, F8, OUT_BF16>::USE && interior && (OUT_BF16 ? vec16_store : vec_store)) {
-      if constexpr (VEC && Staging<BM, BN, NW, F8, OUT_BF16>::USE) {
+    if (LOADS == kLoadRing && Staging<BM, BN, NW, F8, OUT_BF16>::USE && interior && (OUT_BF16 ? vec16_store : vec_store)) {
+      if constexpr (LOADS == kLoadRing && Staging<BM, BN, NW, F8, OUT_BF16>::USE) {
         store_tile_staged<BM, BN, NW, F8, OUT_BF16>(p, acc, m0, n0, lstride, wm, wn, wave, lane_t, lds_addr(smem),
                                                     fused ? 1 : 0);
         // every wave has read its staging rows before the next task's loads

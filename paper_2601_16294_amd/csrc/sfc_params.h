@@ -42,7 +42,7 @@ hipError_t launch_sfc_order(int gm, int gn, int order, int32_t* dev_out, hipStre
 enum Loads {
   kLoadElements = 0,  // element by element (K or N below 8, or leading dimensions past the 32-bit offsets)
   kLoadRing = 1,      // 16-byte aligned rows, straight from memory into LDS (vector_loads_ok)
-  kLoadAny = 2,       // any alignment, 16-byte loads through registers (any_loads_ok)
+  kLoadAny = 2,       // the same at any alignment, a ragged last K block through registers (any_loads_ok)
 };
 
 // One compiled GEMM kernel.

@@ -128,11 +128,11 @@ inline bool vector_loads_ok(const void* A, int64_t lda, const void* B, int64_t l
          ldb < ((int64_t)1 << 22);
 }
 
-// 16-byte loads at element alignment, staged in registers: a chunk that would
-// run past its row's end starts 8 elements before that end, so rows need 8
-// elements, and byte offsets within a block (256 rows of A, 64 of B) are 32-bit.
+// 16-byte loads at element alignment: a last chunk that would run past its row's
+// end is loaded from 8 elements before that end, so rows need 8 elements; per-lane
+// byte offsets within a block (256 rows of A, 64 of B) are 32-bit, as above.
 inline bool any_loads_ok(int64_t lda, int64_t ldb, int64_t K, int64_t N) {
-  return K >= 8 && N >= 8 && lda < ((int64_t)1 << 22) && ldb < ((int64_t)1 << 24);
+  return K >= 8 && N >= 8 && lda < ((int64_t)1 << 20) && ldb < ((int64_t)1 << 22);
 }
 
 // fp8 (OCP E4M3) operands take the 16-byte load path only: 16-byte aligned

@@ -294,13 +294,13 @@ struct Split {
 int plan_tail_split(DeviceState& st, const Plan& pl, int64_t M, int64_t N, int64_t K, const void* A,
                     int64_t lda, const void* B, int64_t ldb, bool ob, Split* sp) {
   sp->on = false;
-  if (pl.ce != 1 || pl.loads != sfc::kLoadRing) return SFC_OK;
+  if (pl.ce != 1 || pl.loads == sfc::kLoadElements) return SFC_OK;
   int half;
   if (pl.tile == sfc::kT256x256) half = sfc::kT128x256;
   else if (pl.tile == sfc::kT256x128) half = sfc::kT128x128;
   else return SFC_OK;
   int occ2 = 1;
-  int rc = get_occupancy(st, {half, ob, sfc::kLoadRing}, &occ2);
+  int rc = get_occupancy(st, {half, ob, pl.loads}, &occ2);
   if (rc != SFC_OK) return rc;
   const int64_t half_rows = sfc::ceil_div(M, sfc::tile_bm(half));
   const int w = sfc::strip_columns(pl.gm, pl.gn, (int64_t)st.num_cus * pl.occ, half_rows,
@@ -316,8 +316,10 @@ int plan_tail_split(DeviceState& st, const Plan& pl, int64_t M, int64_t N, int64
   q.ce = 1;
   q.nk = pl.nk;
   q.occ = occ2;
-  q.loads = sfc::kLoadRing;
-  if (!sfc::vector_loads_ok(A, lda, static_cast<const uint16_t*>(B) + n1, ldb, K, N - n1)) return SFC_OK;
+  // n1 is a multiple of 128, so the strip's B is aligned as B is, and its last
+  // columns need 8 elements of their own only at any alignment
+  q.loads = pl.loads;
+  if (pl.loads == sfc::kLoadAny && !sfc::any_loads_ok(lda, ldb, K, N - n1)) return SFC_OK;
   q.grid = (int)((int64_t)q.gm * q.gn);
   sp->w = w;
   sp->on = true;

@@ -1,7 +1,7 @@
-"""The any-alignment path (16-byte loads at element alignment, staged in
-registers): the ends of rows, where a chunk is loaded early and shifted, the
-last rows, the last K block of a layer, and the limits where the path begins and
-ends.  Integer operands make every sum exact in fp32 (|sum| <= 16 K < 2^24), so
+"""The any-alignment path (16-byte loads at element alignment into the LDS ring,
+a ragged last K block through registers): the ends of rows, where a chunk is
+loaded early and shifted, the last rows, the last K block of a layer, and the
+limits where the path begins and ends.  Integer operands make every sum exact in fp32 (|sum| <= 16 K < 2^24), so
 results are compared bit for bit; padding holds NaN, so an element used from
 outside a row shows."""
 import numpy as np
@@ -56,8 +56,8 @@ def test_layers(c):
 
 
 def test_leading_dimension_limit():
-    # 2^22 - 1 is the last leading dimension of A with 32-bit offsets in a block
-    for lda in ((1 << 22) - 1, 1 << 22):
+    # 2^20 - 1 is the last leading dimension of A the ring's 32-bit offsets take
+    for lda in ((1 << 20) - 1, 1 << 20, (1 << 22) - 1, 1 << 22):
         M, N, K = 3, 40, 72
         A = draw(M, K, ("int", -4, 4), 2500)
         B = draw(K, N, ("int", -4, 4), 2501)
@@ -67,3 +67,10 @@ def test_leading_dimension_limit():
         sg().sfc_gemm_ex(big[:, :K], upload(B), C)
         want = obf16.bf16_to_f64(A).astype(np.int64) @ obf16.bf16_to_f64(B).astype(np.int64)
         assert np.array_equal(to_host(C), want.astype(np.float64)), lda
+
+
+# a last round of half-height blocks (a strip of block columns of its own), whose
+# last columns may be fewer than the 8 that a shifted chunk needs
+@pytest.mark.parametrize("N", [256 * 65 - 255, 256 * 65 - 250, 256 * 65 - 1])
+def test_half_height_strip(N):
+    check(1021, N, 77, "auto", 1, "f32", 77, N, N, 2600)
