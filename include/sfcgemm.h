@@ -257,7 +257,8 @@ int sfc_gemm_f8_fmt_ex(int64_t M, int64_t N, int64_t K,
  * sfc_gemm_plan -- what sfc_gemm_ex would launch, without launching
  * (fp32 output, 16-byte aligned operands).  ca_layers may be SFC_CA_AUTO and
  * tile SFC_TILE_AUTO; the plan then shows the model's choice (for the whole
- * grid: a half-height strip that SFC_TILE_AUTO may add is not shown).
+ * grid: a half-height strip that SFC_TILE_AUTO may add is not shown, nor the
+ * small-block kernel that SFC_TILE_AUTO uses for small products and few rows).
  *   plan[0] = BM, plan[1] = BN, plan[2] = gm, plan[3] = gn, plan[4] = c_eff,
  *   plan[5] = number of persistent workgroups, plan[6] = workgroups per CU.
  * Needs a device (it queries the CU count and kernel occupancy).

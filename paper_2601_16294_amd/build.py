@@ -22,7 +22,7 @@ LIB = os.path.join(PKG, "libsfcgemm.so")
 # longest first
 SOURCES = ["sfc_gemm_256x256_f32.hip", "sfc_gemm_256x256_bf16.hip", "sfc_gemm_256x128.hip", "sfc_gemm_128x256.hip",
            "sfc_gemm_f8_256x256.hip", "sfc_gemm_f8_128x256.hip", "sfc_gemm_128x128.hip", "sfc_gemm_general.hip",
-           "sfc_gemm.hip", "sfc_order.hip",
+           "sfc_gemm.hip", "sfc_small.hip", "sfc_order.hip",
            "sfc_reduce.hip", "sfc_probe.hip", "sfc_model.cpp", "sfcgemm_api.cpp"]
 ARCH = "gfx950"
 

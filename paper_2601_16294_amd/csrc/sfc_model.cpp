@@ -79,4 +79,49 @@ ModelChoice model_choose(int64_t M, int64_t N, int64_t K, int out_bytes, int num
   return best;
 }
 
+// Both kernels' times in microseconds, from fits to about 70 measured calls (M, N
+// 1 .. 2048, K 8 .. 65536): most within 15 %.  The small-block kernel takes 3 us for the
+// launch, the first loads and the end; `round` per 256 of K (64 per wave; the first
+// value with few workgroups, the second with one on every CU; cold operands, too
+// large to lie in a cache, arrive more slowly); operands from memory at 5.2 TB/s
+// (128-byte row segments of B; the curve kernel's 512-byte ones reach 6.0); with
+// several layers 2.2 us for the count's round trip and the last workgroup's read
+// of a block's copies at about 30 bytes per ns.
+SmallChoice small_choose(int64_t M, int64_t N, int64_t K, int out_bytes, int num_cus, int ca_layers, bool layers_ok) {
+  SmallChoice best{0, 1, 1e300};
+  // more blocks than CUs of the tallest shape (a second round of workgroups would
+  // cost more than the curve kernel's larger blocks)
+  if (K < 8 || cdiv(M, 64) * cdiv(N, 64) > num_cus) return best;
+  static const int occ[4] = {2, 1, 1, 1};
+  const ModelChoice old = model_choose(M, N, K, out_bytes, num_cus, occ, -1, ca_layers);
+  const double in_bytes = 2.0 * ((double)M * (double)K + (double)K * (double)N);
+  const double mn = (double)M * (double)N;
+  double old_us = old.clk / 2100.0;
+  const double old_mem = 4.0 + in_bytes / 6.0e6 + (old.layers > 1 ? 4.0 + old.layers * mn * 8.0 / 4.0e6 : 0.0);
+  if (old_mem > old_us) old_us = old_mem;
+  static const double kLow[3] = {0.42, 0.50, 0.62}, kHigh[3] = {0.60, 0.66, 0.86}, kCold[3] = {0.90, 0.95, 1.05};
+  const int64_t nk = cdiv(K, 64);
+  for (int i = 0; i < 3; ++i) {
+    const int fm = 1 << i;
+    const int64_t tiles = cdiv(M, 16 * fm) * cdiv(N, 64);
+    // layers only where the curve kernel would use them too
+    const int max_layers = layers_ok && ca_layers == 0 && old.layers > 1 ? kModelMaxLayers : 1;
+    for (int c = 1; c <= max_layers && tiles * c <= num_cus; c *= 2) {
+      if (c > 1 && nk < 8 * c) break;               // at least two stages per wave
+      const double rounds = (double)cdiv(nk, 4 * c);
+      const double busy = (double)(tiles * c) / (double)num_cus;
+      double per = kLow[i] + (kHigh[i] - kLow[i]) * busy;
+      const double arrive = in_bytes > 60e6 ? 1.3 * kCold[i] : in_bytes > 16e6 ? kCold[i] : 0.0;
+      if (per < arrive) per = arrive;
+      double us = rounds * per;
+      if (us < in_bytes / 5.2e6) us = in_bytes / 5.2e6;
+      us += 3.0 + mn * out_bytes / 4.0e6;
+      if (c > 1) us += 2.2 + (double)(fm * c) * 4096.0 / 30.0e3;
+      if (us < best.us) best = SmallChoice{fm, c, us};
+    }
+  }
+  if (best.us >= old_us) best.fm = 0;
+  return best;
+}
+
 }  // namespace sfc

@@ -63,6 +63,24 @@ hipError_t launch_gemm(const Variant& v, const GemmParams& p, int grid, hipStrea
 // Workgroups of the given kernel that fit on one CU.
 hipError_t gemm_occupancy(const Variant& v, int* blocks_per_cu);
 
+// One launch of the small-block kernel (sfc_small.hip): blocks of 16*fm rows
+// (fm = 1, 2, 4) x 64 columns, `layers` ranges of K.
+struct SmallParams {
+  int M, N, K;
+  int gm, gn, layers;
+  int steps;                 // whole 32-deep steps of K that the LDS ring takes
+  int tail;                  // 1: one more step, through registers
+  const uint16_t* A;
+  int64_t lda;
+  const uint16_t* B;
+  int64_t ldb;
+  void* C;
+  int64_t ldc;
+  float* W;                  // layers > 1: gm*gn*layers copies of 16*fm x 64
+  int32_t* counters;         // layers > 1: one per block, zero between launches
+};
+hipError_t launch_small(const SmallParams& p, int fm, bool out_bf16, hipStream_t stream);
+
 // p[0 .. n) = v (a fill kernel: usable where a memset node is not wanted).
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t stream);
 

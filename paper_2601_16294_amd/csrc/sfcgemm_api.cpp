@@ -360,6 +360,43 @@ int launch_plan(const Plan& pl, const int32_t* table, int64_t M, int64_t N, int6
   return SFC_OK;
 }
 
+// Whether a call whose block shape is the library's to choose runs on the
+// small-block kernel (fm = 0: no), and how.
+sfc::SmallChoice small_choice(const DeviceState& st, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool ob,
+                              int ca_layers, bool layers_ok) {
+  if (ca_layers > 1 || !sfc::any_loads_ok(lda, ldb, K, N)) return sfc::SmallChoice{0, 1, 0.0};
+  return sfc::small_choose(M, N, K, ob ? 2 : 4, st.num_cus, ca_layers, layers_ok);
+}
+
+// One launch of the small-block kernel.  Must be called with g_mu held.
+int launch_small_plan(DeviceState& st, int fm, int layers, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda,
+                      const void* B, int64_t ldb, void* C, int64_t ldc, bool ob, hipStream_t stream) {
+  sfc::SmallParams p;
+  p.M = (int)M; p.N = (int)N; p.K = (int)K;
+  p.gm = (int)sfc::ceil_div(M, 16 * fm);
+  p.gn = (int)sfc::ceil_div(N, 64);
+  p.layers = layers;
+  // a step whose rows or row ends the ring may not take goes through registers
+  p.tail = (K % 32 != 0 || N % 8 != 0) ? 1 : 0;
+  p.steps = (int)sfc::ceil_div(K, 32) - p.tail;
+  p.A = reinterpret_cast<const uint16_t*>(A); p.lda = lda;
+  p.B = reinterpret_cast<const uint16_t*>(B); p.ldb = ldb;
+  p.C = C; p.ldc = ldc;
+  p.W = nullptr;
+  p.counters = nullptr;
+  if (layers > 1) {
+    const int64_t cells = (int64_t)p.gm * p.gn;
+    void* W = nullptr;
+    int rc = stream_workspace(st, stream, (size_t)cells * (size_t)layers * (size_t)(16 * fm * 64) * 4u, &W);
+    if (rc == SFC_OK) rc = stream_counters(st, stream, cells, &p.counters);
+    if (rc != SFC_OK) return rc;
+    p.W = static_cast<float*>(W);
+  }
+  hipError_t e = sfc::launch_small(p, fm, ob, stream);
+  if (e != hipSuccess) return hip_fail(e, "small GEMM launch");
+  return SFC_OK;
+}
+
 // How the layer copies of a call with c_eff > 1 are summed.
 enum Reduce { kReduceSeparate = 0, kReduceFused = 1 };
 
@@ -380,6 +417,12 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const
   DeviceState* st = nullptr;
   int rc = device_state(&st);
   if (rc != SFC_OK) return rc;
+  if (tile == SFC_TILE_AUTO && !f8) {
+    // a caller's workspace is for the curve kernel's layer copies: one layer then
+    const sfc::SmallChoice sm = small_choice(*st, M, N, K, lda, ldb, ob, ca_layers, ws == nullptr);
+    if (sm.fm)
+      return launch_small_plan(*st, sm.fm, sm.layers, M, N, K, A, lda, B, ldb, C, ldc, ob, stream);
+  }
   Plan pl;
   rc = make_plan(*st, M, N, K, A, lda, B, ldb, ob, ca_layers, tile, &pl, f8);
   if (rc != SFC_OK) return rc;
@@ -487,6 +530,11 @@ int gemm_noalloc_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t ld
   int32_t* tables = reinterpret_cast<int32_t*>(base + kNoAllocTableOffset);
   float* W = reinterpret_cast<float*>(base);
 
+  if (tile == SFC_TILE_AUTO) {
+    // one layer needs no memory beyond the caller's
+    const sfc::SmallChoice sm = small_choice(*st, M, N, K, lda, ldb, ob, ca_layers, false);
+    if (sm.fm) return launch_small_plan(*st, sm.fm, 1, M, N, K, A, lda, B, ldb, C, ldc, ob, stream);
+  }
   Plan pl;
   rc = make_plan(*st, M, N, K, A, lda, B, ldb, ob, ca_layers, tile, &pl);
   if (rc != SFC_OK) return rc;
