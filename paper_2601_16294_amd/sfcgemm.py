@@ -159,11 +159,39 @@ def _matrix(t, name):
     return t.data_ptr(), t.shape[0], t.shape[1], ld
 
 
-def _stream_handle(stream) -> Optional[int]:
+def _current_raw_stream():
+    """torch's accessor of a device's current stream handle, without a Stream object
+    (2.9 -> 0.4 us a call), or None if this torch has none."""
     import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return stream.cuda_stream
+    return getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream_handle(stream) -> Optional[int]:
+    if stream is not None:
+        return stream.cuda_stream
+    raw = _cached(_current_raw_stream)
+    current_device, _ = _cached(_torch_calls)
+    if raw is not None:
+        return raw(current_device())
+    import torch
+    return torch.cuda.current_stream().cuda_stream
+
+
+def _torch_calls():
+    import torch
+    return torch.cuda.current_device, torch.Tensor
+
+
+_CACHE = {}
+
+
+def _cached(make):
+    """make()'s value (types and functions of torch), made on first use: torch is
+    imported by the first call that needs it and looked up once."""
+    v = _CACHE.get(make)
+    if v is None and make not in _CACHE:
+        v = _CACHE[make] = make()
+    return v
 
 
 def _operands(A, B, C, what: str, in_types, in_name: str, out_types):
@@ -172,6 +200,24 @@ def _operands(A, B, C, what: str, in_types, in_name: str, out_types):
     stride and matching shapes, A and B hold `in_name` elements, C's dtype is
     one of `out_types`, and all three live on the current CUDA device.
     Returns (pa, lda, pb, ldb, pc, ldc, M, N, K, out_type)."""
+    current_device, Tensor = _cached(_torch_calls)
+    # good operands in one pass (a small call is bound by its host time: 4.1 -> 1.9 us
+    # for these checks); anything else goes through the checks one by one below,
+    # which name what is wrong
+    if (isinstance(A, Tensor) and isinstance(B, Tensor) and isinstance(C, Tensor)
+            and A.dim() == 2 and B.dim() == 2 and C.dim() == 2
+            and A.dtype in in_types and B.dtype in in_types and C.dtype in out_types
+            and A.is_cuda and B.is_cuda and C.is_cuda):
+        M, K = A.shape
+        K2, N = B.shape
+        a0, a1 = A.stride()
+        b0, b1 = B.stride()
+        c0, c1 = C.stride()
+        dev = current_device()
+        if (K2 == K and C.shape == (M, N) and (a1 == 1 or K <= 1) and ((b1 == 1 and c1 == 1) or N <= 1)
+                and A.get_device() == dev and B.get_device() == dev and C.get_device() == dev):
+            return (A.data_ptr(), a0 if M > 1 else max(K, 1), B.data_ptr(), b0 if K > 1 else max(N, 1), C.data_ptr(),
+                    c0 if M > 1 else max(N, 1), M, N, K, SFC_OUT_F32 if C.dtype == _cached(_f32_type) else SFC_OUT_BF16)
     import torch
     for t, n in ((A, "A"), (B, "B"), (C, "C")):
         if not isinstance(t, torch.Tensor):
@@ -198,6 +244,11 @@ def _operands(A, B, C, what: str, in_types, in_name: str, out_types):
     return pa, lda, pb, ldb, pc, ldc, M, N, K, out
 
 
+def _f32_type():
+    import torch
+    return torch.float32
+
+
 def _bf16_types():
     import torch
     return (torch.bfloat16, torch.int16, torch.uint16)
@@ -208,9 +259,19 @@ def _f8_types():
     return (torch.uint8, torch.int8, torch.float8_e4m3fn, torch.float8_e5m2)
 
 
-def _out_types(*names):
+def _out_f32():
     import torch
-    return tuple(getattr(torch, n) for n in names)
+    return (torch.float32,)
+
+
+def _out_bf16():
+    import torch
+    return (torch.bfloat16,)
+
+
+def _out_either():
+    import torch
+    return (torch.float32, torch.bfloat16)
 
 
 def _workspace(workspace):
@@ -225,8 +286,8 @@ def sfc_gemm_ex(A, B, C, ca_layers: int = 1, tile: str = "auto", order: str = "h
                 sched: str = "interleaved", workspace=None, stream=None) -> None:
     """C = A @ B on the GPU.  A: (M, K) bf16, B: (K, N) bf16, C: (M, N) float32
     or bfloat16 (the output type), all CUDA tensors with unit column stride."""
-    pa, lda, pb, ldb, pc, ldc, M, N, K, out = _operands(A, B, C, "sfc_gemm_ex", _bf16_types(), "bf16 patterns",
-                                                        _out_types("float32", "bfloat16"))
+    pa, lda, pb, ldb, pc, ldc, M, N, K, out = _operands(A, B, C, "sfc_gemm_ex", _cached(_bf16_types), "bf16 patterns",
+                                                        _cached(_out_either))
     ws_ptr, ws_bytes = _workspace(workspace)
     _check(lib.sfc_gemm_ex(M, N, K, pa, lda, pb, ldb, pc, ldc, out, ca_layers, TILES[tile],
                            ORDERS[order], SCHEDS[sched], ws_ptr, ws_bytes, _stream_handle(stream)),
@@ -237,8 +298,8 @@ def sfc_gemm_fused_ex(A, B, C, ca_layers: int = 1, tile: str = "auto", order: st
                       sched: str = "interleaved", workspace=None, stream=None) -> None:
     """As sfc_gemm_ex, with the sum of the layer copies done inside the GEMM
     launch by the last workgroup to finish each block."""
-    pa, lda, pb, ldb, pc, ldc, M, N, K, out = _operands(A, B, C, "sfc_gemm_fused_ex", _bf16_types(),
-                                                        "bf16 patterns", _out_types("float32", "bfloat16"))
+    pa, lda, pb, ldb, pc, ldc, M, N, K, out = _operands(A, B, C, "sfc_gemm_fused_ex", _cached(_bf16_types),
+                                                        "bf16 patterns", _cached(_out_either))
     ws_ptr, ws_bytes = _workspace(workspace)
     _check(lib.sfc_gemm_fused_ex(M, N, K, pa, lda, pb, ldb, pc, ldc, out, ca_layers, TILES[tile],
                                  ORDERS[order], SCHEDS[sched], ws_ptr, ws_bytes, _stream_handle(stream)),
@@ -255,8 +316,8 @@ def sfc_gemm_noalloc_ex(A, B, C, ca_layers: int = 1, tile: str = "auto", order: 
     allocate: the library's static per-GPU array holds the layer copies (at
     most NOALLOC_WS_BYTES) and the curve tables.  Calls that overlap on one GPU
     race on that array."""
-    pa, lda, pb, ldb, pc, ldc, M, N, K, out = _operands(A, B, C, "sfc_gemm_noalloc_ex", _bf16_types(),
-                                                        "bf16 patterns", _out_types("float32", "bfloat16"))
+    pa, lda, pb, ldb, pc, ldc, M, N, K, out = _operands(A, B, C, "sfc_gemm_noalloc_ex", _cached(_bf16_types),
+                                                        "bf16 patterns", _cached(_out_either))
     _check(lib.sfc_gemm_noalloc_ex(M, N, K, pa, lda, pb, ldb, pc, ldc, out, ca_layers, TILES[tile],
                                    ORDERS[order], SCHEDS[sched], _stream_handle(stream)),
            "sfc_gemm_noalloc_ex")
@@ -273,8 +334,8 @@ def sfc_gemm_f8_ex(A, B, C, ca_layers: int = 1, tile: str = "auto", order: str =
     each in its format ("e4m3" or "e5m2"); C: (M, N) float32 or bfloat16, all
     with unit column stride.  Both formats E4M3 call sfc_gemm_f8_ex, any other
     pair sfc_gemm_f8_fmt_ex."""
-    pa, lda, pb, ldb, pc, ldc, M, N, K, out = _operands(A, B, C, "sfc_gemm_f8_ex", _f8_types(), "fp8 bytes",
-                                                        _out_types("float32", "bfloat16"))
+    pa, lda, pb, ldb, pc, ldc, M, N, K, out = _operands(A, B, C, "sfc_gemm_f8_ex", _cached(_f8_types), "fp8 bytes",
+                                                        _cached(_out_either))
     fa, fb = FP8_FORMATS[a_format], FP8_FORMATS[b_format]
     ws_ptr, ws_bytes = _workspace(workspace)
     if fa == 0 and fb == 0:
@@ -295,15 +356,15 @@ def to_device_u8(bits: np.ndarray, device="cuda"):
 
 def sfc_gemm(A, B, C, ca_layers: int = 1, stream=None) -> None:
     """C (float32) = A @ B with the default tile choice, curve order and schedule."""
-    pa, lda, pb, ldb, pc, ldc, M, N, K, _ = _operands(A, B, C, "sfc_gemm", _bf16_types(), "bf16 patterns",
-                                                      _out_types("float32"))
+    pa, lda, pb, ldb, pc, ldc, M, N, K, _ = _operands(A, B, C, "sfc_gemm", _cached(_bf16_types), "bf16 patterns",
+                                                      _cached(_out_f32))
     _check(lib.sfc_gemm(M, N, K, pa, lda, pb, ldb, pc, ldc, ca_layers, _stream_handle(stream)), "sfc_gemm")
 
 
 def sfc_gemm_bf16out(A, B, C, ca_layers: int = 1, stream=None) -> None:
     """C (bfloat16) = A @ B with the default tile choice, curve order and schedule."""
-    pa, lda, pb, ldb, pc, ldc, M, N, K, _ = _operands(A, B, C, "sfc_gemm_bf16out", _bf16_types(),
-                                                      "bf16 patterns", _out_types("bfloat16"))
+    pa, lda, pb, ldb, pc, ldc, M, N, K, _ = _operands(A, B, C, "sfc_gemm_bf16out", _cached(_bf16_types),
+                                                      "bf16 patterns", _cached(_out_bf16))
     _check(lib.sfc_gemm_bf16out(M, N, K, pa, lda, pb, ldb, pc, ldc, ca_layers, _stream_handle(stream)),
            "sfc_gemm_bf16out")
 
