@@ -292,7 +292,7 @@ struct Split {
 };
 
 int plan_tail_split(DeviceState& st, const Plan& pl, int64_t M, int64_t N, int64_t K, const void* A,
-                    int64_t lda, const void* B, int64_t ldb, bool ob, Split* sp) {
+                    int64_t lda, const void* B, int64_t ldb, bool ob, int f8, Split* sp) {
   sp->on = false;
   if (pl.ce != 1 || pl.loads == sfc::kLoadElements) return SFC_OK;
   int half;
@@ -300,7 +300,7 @@ int plan_tail_split(DeviceState& st, const Plan& pl, int64_t M, int64_t N, int64
   else if (pl.tile == sfc::kT256x128) half = sfc::kT128x128;
   else return SFC_OK;
   int occ2 = 1;
-  int rc = get_occupancy(st, {half, ob, pl.loads}, &occ2);
+  int rc = get_occupancy(st, {half, ob, pl.loads, f8}, &occ2);
   if (rc != SFC_OK) return rc;
   const int64_t half_rows = sfc::ceil_div(M, sfc::tile_bm(half));
   const int w = sfc::strip_columns(pl.gm, pl.gn, (int64_t)st.num_cus * pl.occ, half_rows,
@@ -430,8 +430,8 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const
   // the block shape is the library's to choose: a half-height strip may take
   // a partial last round
   Split sp;
-  if (tile == SFC_TILE_AUTO && !f8) {
-    rc = plan_tail_split(*st, pl, M, N, K, A, lda, B, ldb, ob, &sp);
+  if (tile == SFC_TILE_AUTO) {
+    rc = plan_tail_split(*st, pl, M, N, K, A, lda, B, ldb, ob, f8, &sp);
     if (rc != SFC_OK) return rc;
   }
   const Fuse none;
@@ -446,11 +446,11 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const
     rc = get_table(*st, main.gm, main.gn, order, stream, &t_main);
     if (rc == SFC_OK) rc = get_table(*st, sp.strip.gm, sp.strip.gn, order, stream, &t_strip);
     if (rc != SFC_OK) return rc;
-    rc = launch_plan(main, t_main, M, n1, K, A, lda, B, ldb, C, ldc, 0, ob, sched, none, stream, 0);
+    rc = launch_plan(main, t_main, M, n1, K, A, lda, B, ldb, C, ldc, 0, ob, sched, none, stream, f8);
     if (rc != SFC_OK) return rc;
     const size_t esz = ob ? 2 : 4;
-    return launch_plan(sp.strip, t_strip, M, N - n1, K, A, lda, static_cast<const uint16_t*>(B) + n1, ldb,
-                       static_cast<char*>(C) + (size_t)n1 * esz, ldc, 0, ob, sched, none, stream, 0);
+    return launch_plan(sp.strip, t_strip, M, N - n1, K, A, lda, static_cast<const char*>(B) + n1 * (f8 ? 1 : 2), ldb,
+                       static_cast<char*>(C) + (size_t)n1 * esz, ldc, 0, ob, sched, none, stream, f8);
   }
 
   const int32_t* table = nullptr;
@@ -542,7 +542,7 @@ int gemm_noalloc_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t ld
     return set_error(SFC_ERR_WORKSPACE, "sfc_gemm_noalloc_ex: the planned layer copies exceed its workspace");
   Split sp;
   if (tile == SFC_TILE_AUTO) {
-    rc = plan_tail_split(*st, pl, M, N, K, A, lda, B, ldb, ob, &sp);
+    rc = plan_tail_split(*st, pl, M, N, K, A, lda, B, ldb, ob, 0, &sp);
     if (rc != SFC_OK) return rc;
   }
   Plan main = pl;

@@ -190,6 +190,24 @@ def test_auto_layers(M, N, K):
         assert pick["layers"] > 1
 
 
+# a partial last round of 256x256 blocks leaves its last block columns to
+# half-height blocks of their own launch (SFC_TILE_AUTO): same bits as whole blocks
+@pytest.mark.parametrize("M,N,K,out,fa,fb", [(4000, 256 * 52 - 240, 400, "f32", "e4m3", "e4m3"),
+                                             (4096, 256 * 56, 128, "bf16", "e5m2", "e4m3")])
+def test_half_height_strip(M, N, K, out, fa, fb):
+    A = draw_fp8(M, K, ("normal", 0.0, 1.0), 9101, fmt=fa)
+    B = draw_fp8(K, N, ("normal", 0.0, 1.0), 9102, fmt=fb)
+    dA, dB = up8(A), up8(B)
+    dtype = torch.float32 if out == "f32" else torch.bfloat16
+    C = {}
+    for tile in ("auto", "256x256"):
+        C[tile] = torch.full((M, N + 16), float("nan"), dtype=dtype, device="cuda")
+        sg().sfc_gemm_f8_ex(dA, dB, C[tile][:, :N], tile=tile, a_format=fa, b_format=fb)
+    torch.cuda.synchronize()
+    assert sg().sfc_gemm_f8_plan(M, N, K, 1, "auto")["BM"] == 256
+    assert np.array_equal(raw_bits(C["auto"]), raw_bits(C["256x256"]))
+
+
 # ---- OCP E5M2 and mixed formats (sfc_gemm_f8_fmt_ex) ---------------------------
 
 FMT_PAIRS = [("e5m2", "e5m2"), ("e4m3", "e5m2"), ("e5m2", "e4m3")]
