@@ -4,6 +4,7 @@
 #include <cmath>
 
 #include "sfc_params.h"
+#include "sfc_validate.h"
 
 namespace sfc {
 
@@ -77,6 +78,23 @@ ModelChoice model_choose(int64_t M, int64_t N, int64_t K, int out_bytes, int num
     }
   }
   return best;
+}
+
+bool strip_beats_128x256(int64_t M, int64_t N, int64_t nk, int out_bytes, int num_cus, const ModelChoice& ch,
+                         const ModelConst& k) {
+  if (ch.tile != kT128x256 || ch.layers != 1) return false;
+  const int64_t gm = cdiv(M, 256), gn = cdiv(N, 256);
+  if (gm * gn >= ((int64_t)1 << 30)) return false;
+  const int w = strip_columns((int)gm, (int)gn, num_cus, cdiv(M, 128), num_cus);
+  if (w == 0) return false;
+  const int64_t full = gm * gn / num_cus, left = gm * gn % num_cus;
+  if (full < 2 && 4 * left < num_cus) return false;
+  const double g = 2.0 * 256.0 * 256.0 * 64.0 / k.flops_per_clk_cu;
+  const double t_main = g / k.rate[kT256x256], t_strip = 0.5 * g / k.rate[kT128x256];
+  const double rounds = (double)cdiv(gm * (gn - w), num_cus);
+  const double clk = 2.0 * k.launch_clk + (double)nk * (rounds * t_main + t_strip) +
+                     (double)M * (double)N * out_bytes / k.hbm_bytes_per_clk;
+  return clk < 0.955 * ch.clk;
 }
 
 // Both kernels' times in microseconds, from fits to about 70 measured calls (M, N

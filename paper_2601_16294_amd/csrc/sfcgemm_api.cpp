@@ -224,6 +224,8 @@ int make_plan(DeviceState& st, int64_t M, int64_t N, int64_t K, const void* A, i
         const sfc::ModelChoice ch = sfc::model_choose(M, N, k_equiv, ob ? 2 : 4, st.num_cus, occ, t, ca_layers);
         if (best.tile < 0 || ch.clk < best.clk) best = ch;
       }
+      if (tile < 0 && sfc::strip_beats_128x256(M, N, k_equiv / sfc::kBK, ob ? 2 : 4, st.num_cus, best))
+        best.tile = sfc::kT256x256;
       tile = best.tile;
       layers = best.layers;
     }
@@ -252,9 +254,12 @@ int make_plan(DeviceState& st, int64_t M, int64_t N, int64_t K, const void* A, i
       rc = get_occupancy(st, {t, ob && ca_layers == 1, pl->loads}, &occ[t]);
       if (rc != SFC_OK) return rc;
     }
-    const sfc::ModelChoice ch =
+    sfc::ModelChoice ch =
         sfc::model_choose(M, N, K, ob ? 2 : 4, st.num_cus, occ,
                           tile_api == SFC_TILE_AUTO ? -1 : tile_from_api(tile_api), ca_layers);
+    if (tile_api == SFC_TILE_AUTO && pl->loads != sfc::kLoadElements &&
+        sfc::strip_beats_128x256(M, N, sfc::ceil_div(K, sfc::kBK), ob ? 2 : 4, st.num_cus, ch))
+      ch.tile = sfc::kT256x256;
     pl->tile = ch.tile;
     pl->ce = sfc::effective_layers(K, ch.layers, sfc::kBK);
   } else {

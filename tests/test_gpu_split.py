@@ -63,3 +63,21 @@ def test_strip_matches_single_launch(M, N, K, out, seed):
     for r in (0, M - 1):
         Cr, Rr = ogemm.gemm_ref_rows(A, B, N, K, K, N, row0=r, nrows=1)
         ocheck.assert_gemm_close(to_host(Ca[r:r + 1]), Cr, Rr, f"split {M}x{N}x{K} row {r}")
+
+
+# 256x256 blocks and a strip where the model alone would take 128x256 blocks: the
+# same bits as either shape in one launch
+@pytest.mark.parametrize("M,N,K,out", [(1300, 14336, 4096, "bf16"), (2561, 8001, 4099, "f32"), (4096, 6144, 4096, "f32")])
+def test_strip_instead_of_128x256(M, N, K, out):
+    A = draw(M, K, U, 8501)
+    B = draw(K, N, U, 8502)
+    dA, dB = upload(A), upload(B)
+    dtype = torch.float32 if out == "f32" else torch.bfloat16
+    iview = torch.int32 if out == "f32" else torch.int16
+    C = {t: torch.full((M, N), float("nan"), dtype=dtype, device="cuda") for t in ("auto", "256x256", "128x256")}
+    for t, c in C.items():
+        sg().sfc_gemm_ex(dA, dB, c, tile=t)
+    torch.cuda.synchronize()
+    assert not torch.isnan(C["auto"]).any().item()
+    assert torch.equal(C["auto"].view(iview), C["256x256"].view(iview))
+    assert torch.equal(C["auto"].view(iview), C["128x256"].view(iview))
