@@ -1156,6 +1156,10 @@ __device__ __forceinline__ u32x4 pair_to_row8(const f32x4& x, const f32x4& y) {
   return u32x4{s0[0], s1[0], s0[1], s1[1]};
 }
 
+// 4 elements stored at element alignment.
+template <int ES, typename V>
+struct __attribute__((packed, aligned(ES))) Store4 { V v; };
+
 // Epilogue of the fp8 kernels (MFMA 32x32x64, B fragment first): fragment
 // (i, j) of the wave, lane l, accumulator v holds row 32i + l%32 and column
 // 32j + 8*(v/4) + 4*(l/32) + v%4 -- four runs of 4 consecutive columns.  For
@@ -1223,10 +1227,17 @@ __device__ __forceinline__ void store_tile32(const GemmParams& p, const Acc<BM, 
     for (int j = 0; j < T::FN; ++j)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
+        // 4 columns at element alignment; N is a multiple of 16
         const int64_t c = cb + j * 32 + 8 * g + 4 * h;
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (c + e < p.N) row[c + e] = (OutT)acc[i][j][4 * g + e];
+        const f32x16& a = acc[i][j];
+        if (c >= p.N) continue;
+        if constexpr (OUT_BF16) {
+          const bf16x4 v = {(__bf16)a[4 * g], (__bf16)a[4 * g + 1], (__bf16)a[4 * g + 2], (__bf16)a[4 * g + 3]};
+          reinterpret_cast<Store4<2, bf16x4>*>(row + c)->v = v;
+        } else {
+          const f32x4 v = {a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]};
+          reinterpret_cast<Store4<4, f32x4>*>(row + c)->v = v;
+        }
       }
     if (OUT_BF16) __builtin_amdgcn_sched_barrier(0);
   }
@@ -1274,9 +1285,15 @@ __device__ __forceinline__ void st_f32(float* p, float v, int co) {
 // lane with 16 lanes on one row segment, and stores 16 bytes per lane: a store
 // instruction then covers 1024 / (row bytes) whole row segments instead of 16
 // or 32 rows of 32-64 bytes, and the store path issues it faster (measured on
-// MI355X: about a third less time for the block's stores).  Interior blocks
-// with 16-byte aligned rows only; a sub-block that does not fit the rings at
-// once goes in several row passes.  The caller synchronises the workgroup
+// MI355X: about a third less time for the block's stores).  16-byte aligned rows
+// of C only; edge blocks store the 16-byte pieces that lie inside C (their
+// operands' N is a multiple of 8 bf16 or 16 fp8 elements, so a piece is all in or
+// all out).  Edge blocks stored element by element took longer than the rest of
+// a short-K grid: 5824x2304x184 bf16 out 33.1 -> 15.5 us, 1984x4608x64 f32 31.9 ->
+// 16.4, 2029x7280x624 fp8 44.5 -> 18.8, 1204x1784x2128 f32 27.5 -> 23.2.  The checks are a
+// copy of the store loop of their own (in the interior blocks' loop they cost 1 %
+// on 8192x4096x512).  A sub-block that does not fit the rings at once goes in
+// several row passes.  The caller synchronises the workgroup
 // before the rings are written again.
 template <int BM, int BN, int NW, int F8, bool OUT_BF16>
 struct Staging {
@@ -1310,7 +1327,7 @@ __device__ __forceinline__ u32x4 lds_read16(uint32_t addr) {
 template <int BM, int BN, int NW, int F8, bool OUT_BF16>
 __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const Acc<BM, BN, NW, F8>& acc, int64_t m0,
                                                   int64_t n0, int64_t lstride, int wm, int wn, int wave, int lane,
-                                                  uint32_t lds0, int co) {
+                                                  uint32_t lds0, int co, bool interior) {
   using T = Tile<BM, BN, NW, F8>;
   using S = Staging<BM, BN, NW, F8, OUT_BF16>;
   typedef typename std::conditional<OUT_BF16, __bf16, float>::type OutT;
@@ -1372,19 +1389,24 @@ __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const Acc
     wait_lds_all();
     // whole row segments back out: lane l reads chunk l % CPR of row l / CPR
     const int rr = lane / S::CPR, cc = lane % S::CPR;
+    auto rows_out = [&](auto edge) {
 #pragma unroll
-    for (int t = 0; t < S::PASS_ROWS / S::RPI; t += 4) {
-      u32x4 v[4];
+      for (int t = 0; t < S::PASS_ROWS / S::RPI; t += 4) {
+        u32x4 v[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (t + u < S::PASS_ROWS / S::RPI) v[u] = lds_read16(base + (uint32_t)(((t + u) * S::RPI + rr) * S::RS + cc * 16));
+        for (int u = 0; u < 4; ++u)
+          if (t + u < S::PASS_ROWS / S::RPI) v[u] = lds_read16(base + (uint32_t)(((t + u) * S::RPI + rr) * S::RS + cc * 16));
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (t + u < S::PASS_ROWS / S::RPI) {
-          const int64_t row = row0 + pass * S::PASS_ROWS + (t + u) * S::RPI + rr;
-          st16<!OUT_BF16 && F8 == 0>(out + row * p.ldo + col0 + cc * (16 / S::ES), v[u], co);
-        }
-    }
+        for (int u = 0; u < 4; ++u)
+          if (t + u < S::PASS_ROWS / S::RPI) {
+            const int64_t row = row0 + pass * S::PASS_ROWS + (t + u) * S::RPI + rr;
+            if (!decltype(edge)::value || (row < p.M && col0 + cc * (16 / S::ES) < p.N))
+              st16<!OUT_BF16 && F8 == 0>(out + row * p.ldo + col0 + cc * (16 / S::ES), v[u], co);
+          }
+      }
+    };
+    if (interior) rows_out(std::false_type{});
+    else rows_out(std::true_type{});
     if (pass + 1 < S::PASSES) wait_lds_all();   // this wave's reads are done before its next writes
   }
 }
@@ -1469,9 +1491,10 @@ __device__ __forceinline__ void store_tile(const GemmParams& p, const Acc<BM, BN
   }
 }
 
-// Epilogue of the any-alignment kernels: 16-byte stores at element alignment,
-// whatever the alignment of C's rows; only the 4 (fp32) or 8 (bf16) columns that
-// straddle N are stored element by element.
+// Epilogue of the any-alignment kernels, and of edge blocks or unaligned rows of C
+// in the others: 16-byte stores at element alignment, whatever the alignment of
+// C's rows; only the 4 (fp32) or 8 (bf16) columns that straddle N are stored
+// element by element.
 template <int ES>
 struct __attribute__((packed, aligned(ES))) Store16 { u32x4 v; };
 
@@ -1716,17 +1739,21 @@ __global__ __launch_bounds__(NW * 64, 1) void sfc_gemm_kernel(GemmParams p) {
     // layer copies that this launch reduces itself are stored coherently
     constexpr bool kFusable = !OUT_BF16 && F8 == 0;
     const bool fused = kFusable && p.counters != nullptr;
-    if (LOADS == kLoadRing && Staging<BM, BN, NW, F8, OUT_BF16>::USE && interior && (OUT_BF16 ? vec16_store : vec_store)) {
+    // kernels whose aligned blocks all leave through LDS keep the plain element
+    // stores for unaligned rows of C: the 16-byte form beside them made the register
+    // allocator move accumulators inside the K loop (f32 128x256: +25 % time)
+    constexpr bool kStoreAny = F8 == 0 && (LOADS == kLoadAny || (LOADS == kLoadRing && !Staging<BM, BN, NW, F8, OUT_BF16>::USE));
+    if (LOADS == kLoadRing && Staging<BM, BN, NW, F8, OUT_BF16>::USE && (OUT_BF16 ? vec16_store : vec_store)) {
       if constexpr (LOADS == kLoadRing && Staging<BM, BN, NW, F8, OUT_BF16>::USE) {
         store_tile_staged<BM, BN, NW, F8, OUT_BF16>(p, acc, m0, n0, lstride, wm, wn, wave, lane_t, lds_addr(smem),
-                                                    fused ? 1 : 0);
+                                                    fused ? 1 : 0, interior);
         // every wave has read its staging rows before the next task's loads
         // land in the rings
         wait_lds_all();
         __syncthreads();
       }
-    } else if (LOADS == kLoadAny && !fused) {
-      if constexpr (LOADS == kLoadAny) store_tile_any<BM, BN, NW, OUT_BF16>(p, acc, m0, n0, lstride, wm, wn, lane_t, interior);
+    } else if (kStoreAny && !fused && (LOADS == kLoadAny || !interior || !vec_store)) {
+      if constexpr (kStoreAny) store_tile_any<BM, BN, NW, OUT_BF16>(p, acc, m0, n0, lstride, wm, wn, lane_t, interior);
     } else {
       store_tile<BM, BN, NW, F8, OUT_BF16>(p, acc, m0, n0, lstride, wm, wn, lane_t, interior && vec_store,
                                         interior && vec16_store, fused ? 1 : 0);

@@ -74,3 +74,13 @@ def test_leading_dimension_limit():
 @pytest.mark.parametrize("N", [256 * 65 - 255, 256 * 65 - 250, 256 * 65 - 1])
 def test_half_height_strip(N):
     check(1021, N, 77, "auto", 1, "f32", 77, N, N, 2600)
+
+
+# aligned operands: the rows and columns of edge blocks, stored 16 bytes at a time
+# where C's rows are aligned, and nothing outside C
+@pytest.mark.parametrize("M,N", [(1, 8), (17, 120), (127, 136), (129, 248), (255, 264), (257, 504), (300, 256), (256, 520)])
+@pytest.mark.parametrize("tile", TILES)
+def test_edge_blocks_of_aligned_operands(M, N, tile):
+    for out, pad in (("f32", 4), ("bf16", 8), ("f32", 1), ("bf16", 3)):
+        check(M, N, 136, tile, 1, out, 136, N, N + pad, 2700 + M)
+    check(M, N, 136, tile, 2, "f32", 136, N + 8, N, 2800 + M)

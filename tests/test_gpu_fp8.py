@@ -209,6 +209,21 @@ def test_half_height_strip(M, N, K, out, fa, fb):
     assert np.array_equal(raw_bits(C["auto"]), raw_bits(C["256x256"]))
 
 
+# edge blocks: every element of C and nothing outside it, rows of C aligned or not
+@pytest.mark.parametrize("M,N", [(1, 16), (33, 112), (127, 144), (255, 272), (257, 496), (300, 528)])
+@pytest.mark.parametrize("tile", ["256x256", "128x256"])
+def test_edge_blocks(M, N, tile):
+    K = 160
+    A = draw_e4m3(M, K, ("int", -4, 4), 9201 + M)
+    B = draw_e4m3(K, N, ("int", -4, 4), 9202 + N)
+    Cr, _ = ref(A, B, M, N, K)
+    for out, pad in (("f32", 4), ("bf16", 8), ("f32", 1), ("bf16", 3)):
+        C = to_host(run8(A, B, M, N, K, out, ldc=N + pad, tile=tile))
+        want = obf16.bf16_to_f64(obf16.f32_to_bf16_rne(Cr.astype(np.float32))) if out == "bf16" else Cr
+        assert np.array_equal(C[:, :N], want), (M, N, tile, out, pad)
+        assert np.isnan(C[:, N:]).all()
+
+
 # ---- OCP E5M2 and mixed formats (sfc_gemm_f8_fmt_ex) ---------------------------
 
 FMT_PAIRS = [("e5m2", "e5m2"), ("e4m3", "e5m2"), ("e5m2", "e4m3")]
