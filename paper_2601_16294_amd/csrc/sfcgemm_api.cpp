@@ -369,7 +369,8 @@ int launch_plan(const Plan& pl, const int32_t* table, int64_t M, int64_t N, int6
 // small-block kernel (fm = 0: no), and how.
 sfc::SmallChoice small_choice(const DeviceState& st, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool ob,
                               int ca_layers, bool layers_ok) {
-  if (ca_layers > 1 || !sfc::any_loads_ok(lda, ldb, K, N)) return sfc::SmallChoice{0, 1, 0.0};
+  // (K well inside 32 bits: the kernel's K indices run up to a stage past it)
+  if (ca_layers > 1 || K > ((int64_t)1 << 30) || !sfc::any_loads_ok(lda, ldb, K, N)) return sfc::SmallChoice{0, 1, 0.0};
   return sfc::small_choose(M, N, K, ob ? 2 : 4, st.num_cus, ca_layers, layers_ok);
 }
 
@@ -389,10 +390,21 @@ int launch_small_plan(DeviceState& st, int fm, int layers, int64_t M, int64_t N,
   p.C = C; p.ldc = ldc;
   p.W = nullptr;
   p.counters = nullptr;
-  if (layers > 1) {
-    const int64_t cells = (int64_t)p.gm * p.gn;
+  const int64_t cells = (int64_t)p.gm * p.gn;
+  const size_t ws_bytes = (size_t)cells * (size_t)layers * (size_t)(16 * fm * 64) * 4u;
+  if (layers > 1 && (st.streams[stream].ws_bytes < ws_bytes || st.streams[stream].n_counters < cells)) {
+    // memory allocated while the stream is captured would belong to the graph:
+    // one layer needs none
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
+      (void)hipGetLastError();
+      cap = hipStreamCaptureStatusNone;
+    }
+    if (cap != hipStreamCaptureStatusNone) p.layers = 1;
+  }
+  if (p.layers > 1) {
     void* W = nullptr;
-    int rc = stream_workspace(st, stream, (size_t)cells * (size_t)layers * (size_t)(16 * fm * 64) * 4u, &W);
+    int rc = stream_workspace(st, stream, ws_bytes, &W);
     if (rc == SFC_OK) rc = stream_counters(st, stream, cells, &p.counters);
     if (rc != SFC_OK) return rc;
     p.W = static_cast<float*>(W);

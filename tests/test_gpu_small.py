@@ -80,6 +80,35 @@ def test_layers_on_two_streams():
             assert np.array_equal(to_host(C), want)
 
 
+# captured into a graph on a stream without library memory (one layer then, nothing
+# is allocated) and on a stream that has it; replays beside eager work on the same
+# operands give the eager result each time
+@pytest.mark.parametrize("warm", [False, True])
+def test_graph_capture(warm):
+    M, N, K = 13, 1024, 16384
+    A, B = draw(M, K, ("int", -4, 4), 3900), draw(K, N, ("int", -4, 4), 3901)
+    dA, dB, want = upload(A), upload(B), want_of(A, B, K, N, "f32")
+    C = torch.full((M, N), float("nan"), device="cuda")
+    E = torch.full((M, N), float("nan"), device="cuda")
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        if warm:
+            sg().sfc_gemm(dA, dB, E, ca_layers=0)
+        g = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(g, stream=s):
+            sg().sfc_gemm(dA, dB, C, ca_layers=0)
+        for _ in range(3):
+            C.fill_(float("nan"))
+            g.replay()
+            sg().sfc_gemm(dA, dB, E, ca_layers=0)
+            torch.cuda.synchronize()
+            assert np.array_equal(to_host(C), want)
+            assert np.array_equal(to_host(E), want)
+            E.fill_(float("nan"))
+
+
 # infinities and NaN stay in their rows and columns (a block's neighbours, and K
 # past a ragged end, hold zeros and not other rows' values)
 def test_special_values_stay():
