@@ -55,7 +55,11 @@ extern "C" {
                                     launch (same stream) with 128-row blocks of the
                                     same width, which fill one round in about half
                                     the time; result bits are those of the single
-                                    launch */
+                                    launch.  Small products and few rows with
+                                    ca_layers SFC_CA_AUTO or 1 run on a kernel of
+                                    16-, 32- or 64-row blocks (not with a caller's
+                                    workspace and SFC_CA_AUTO: its layer copies
+                                    are those of sfc_gemm_plan) */
 #define SFC_TILE_128x128 1
 #define SFC_TILE_256x128 2       /* BM = 256, BN = 128 */
 #define SFC_TILE_128x256 3       /* BM = 128, BN = 256 */
@@ -187,7 +191,8 @@ int sfc_gemm_fused_ex(int64_t M, int64_t N, int64_t K,
  * per-stream workspace and cached curve tables it uses one static device
  * array per GPU, held until the process ends: SFC_NOALLOC_WS_BYTES of fp32
  * layer copies and two curve tables of SFC_NOALLOC_MAX_BLOCKS entries, which
- * every call rewrites on `stream` (a small kernel before the GEMM).
+ * every call that runs on the curve kernel rewrites on `stream` (a small kernel
+ * before the GEMM); the small-block kernel's copies and counters lie there too.
  *   Arguments and errors as for sfc_gemm_ex without a workspace, plus:
  *   SFC_ERR_WORKSPACE   sfc_gemm_ws_size(M, N, K, ca_layers) exceeds
  *                       SFC_NOALLOC_WS_BYTES (checked before any HIP call);

@@ -374,9 +374,12 @@ sfc::SmallChoice small_choice(const DeviceState& st, int64_t M, int64_t N, int64
   return sfc::small_choose(M, N, K, ob ? 2 : 4, st.num_cus, ca_layers, layers_ok);
 }
 
-// One launch of the small-block kernel.  Must be called with g_mu held.
+// The small-block kernel; its layer copies and counters lie in (W, counters), the
+// counters zero, or, if W is null, in the stream's own memory.  Must be called
+// with g_mu held.
 int launch_small_plan(DeviceState& st, int fm, int layers, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda,
-                      const void* B, int64_t ldb, void* C, int64_t ldc, bool ob, hipStream_t stream) {
+                      const void* B, int64_t ldb, void* C, int64_t ldc, bool ob, hipStream_t stream,
+                      float* W = nullptr, int32_t* counters = nullptr) {
   sfc::SmallParams p;
   p.M = (int)M; p.N = (int)N; p.K = (int)K;
   p.gm = (int)sfc::ceil_div(M, 16 * fm);
@@ -388,11 +391,11 @@ int launch_small_plan(DeviceState& st, int fm, int layers, int64_t M, int64_t N,
   p.A = reinterpret_cast<const uint16_t*>(A); p.lda = lda;
   p.B = reinterpret_cast<const uint16_t*>(B); p.ldb = ldb;
   p.C = C; p.ldc = ldc;
-  p.W = nullptr;
-  p.counters = nullptr;
+  p.W = W;
+  p.counters = counters;
   const int64_t cells = (int64_t)p.gm * p.gn;
   const size_t ws_bytes = (size_t)cells * (size_t)layers * (size_t)(16 * fm * 64) * 4u;
-  if (layers > 1 && (st.streams[stream].ws_bytes < ws_bytes || st.streams[stream].n_counters < cells)) {
+  if (layers > 1 && !W && (st.streams[stream].ws_bytes < ws_bytes || st.streams[stream].n_counters < cells)) {
     // memory allocated while the stream is captured would belong to the graph:
     // one layer needs none
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -402,12 +405,12 @@ int launch_small_plan(DeviceState& st, int fm, int layers, int64_t M, int64_t N,
     }
     if (cap != hipStreamCaptureStatusNone) p.layers = 1;
   }
-  if (p.layers > 1) {
-    void* W = nullptr;
-    int rc = stream_workspace(st, stream, ws_bytes, &W);
+  if (p.layers > 1 && !W) {
+    void* own = nullptr;
+    int rc = stream_workspace(st, stream, ws_bytes, &own);
     if (rc == SFC_OK) rc = stream_counters(st, stream, cells, &p.counters);
     if (rc != SFC_OK) return rc;
-    p.W = static_cast<float*>(W);
+    p.W = static_cast<float*>(own);
   }
   hipError_t e = sfc::launch_small(p, fm, ob, stream);
   if (e != hipSuccess) return hip_fail(e, "small GEMM launch");
@@ -434,9 +437,10 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const
   DeviceState* st = nullptr;
   int rc = device_state(&st);
   if (rc != SFC_OK) return rc;
-  if (tile == SFC_TILE_AUTO && !f8) {
-    // a caller's workspace is for the curve kernel's layer copies: one layer then
-    const sfc::SmallChoice sm = small_choice(*st, M, N, K, lda, ldb, ob, ca_layers, ws == nullptr);
+  // (a caller's workspace receives the layer copies of the plan: with the layer
+  // count left to the library, that is the curve kernel's)
+  if (tile == SFC_TILE_AUTO && !f8 && !(ws && ca_layers == SFC_CA_AUTO)) {
+    const sfc::SmallChoice sm = small_choice(*st, M, N, K, lda, ldb, ob, ca_layers, true);
     if (sm.fm)
       return launch_small_plan(*st, sm.fm, sm.layers, M, N, K, A, lda, B, ldb, C, ldc, ob, stream);
   }
@@ -500,7 +504,9 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const
 // sfc_gemm_noalloc_ex keeps everything it needs beyond the caller's buffers in
 // this file-scope device array: the layer copies of a ca_layers > 1 call
 // (kNoAllocWsBytes) and the curve tables of its launches (two of at most
-// kNoAllocCells entries: the main grid and the half-height strip).  Each
+// kNoAllocCells entries: the main grid and the half-height strip).  The small-block
+// kernel's copies and counters (a block and layer per CU at most) lie in the same
+// array, its counters in the first table.  Each
 // device holds its own copy until the process ends.  In host code `scratch`
 // only names the array: its address on a device comes from
 // hipGetSymbolAddress, taken once per device with that device current.
@@ -548,9 +554,17 @@ int gemm_noalloc_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t ld
   float* W = reinterpret_cast<float*>(base);
 
   if (tile == SFC_TILE_AUTO) {
-    // one layer needs no memory beyond the caller's
-    const sfc::SmallChoice sm = small_choice(*st, M, N, K, lda, ldb, ob, ca_layers, false);
-    if (sm.fm) return launch_small_plan(*st, sm.fm, 1, M, N, K, A, lda, B, ldb, C, ldc, ob, stream);
+    const sfc::SmallChoice sm = small_choice(*st, M, N, K, lda, ldb, ob, ca_layers, true);
+    const int64_t cells = sfc::ceil_div(M, 16 * (sm.fm ? sm.fm : 1)) * sfc::ceil_div(N, 64);
+    if (sm.fm && sm.layers > 1) {
+      if (cells > kNoAllocCells || (size_t)(cells * sm.layers) * (size_t)(16 * sm.fm * 64) * 4u > kNoAllocWsBytes)
+        return set_error(SFC_ERR_WORKSPACE, "sfc_gemm_noalloc_ex: the planned layer copies exceed its workspace");
+      // the table memory holds what the last call left: counters start from zero
+      hipError_t e = sfc::launch_fill_i32(tables, cells, 0, stream);
+      if (e != hipSuccess) return hip_fail(e, "counter fill");
+    }
+    if (sm.fm)
+      return launch_small_plan(*st, sm.fm, sm.layers, M, N, K, A, lda, B, ldb, C, ldc, ob, stream, W, tables);
   }
   Plan pl;
   rc = make_plan(*st, M, N, K, A, lda, B, ldb, ob, ca_layers, tile, &pl);

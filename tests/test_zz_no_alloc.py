@@ -58,6 +58,42 @@ def test_noalloc_matches_ex_two_calls(seq):
         assert sg().sfc_gemm_plan(1024, 1024, 16384, 0, "auto")["layers"] > 1
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 1024, 16384), (16, 14336, 4096), (33, 515, 8197), (64, 64, 4096)])
+def test_noalloc_matches_ex_few_rows(M, N, K):
+    """Few rows, the layer count left to the library: the same bits as sfc_gemm_ex,
+    also after a call that left other values in the static array."""
+    A, B = draw(M, K, ("normal", 0.0, 1.0), 9950), draw(K, N, ("normal", 0.0, 0.02), 9951)
+    dA, dB = upload(A), upload(B)
+    Ce = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    sg().sfc_gemm_ex(dA, dB, Ce, ca_layers=0)
+    other = torch.zeros((2000, 1024), dtype=torch.bfloat16, device="cuda")
+    scratch_user = torch.empty((2000, 2000), dtype=torch.float32, device="cuda")
+    for _ in range(2):
+        sg().sfc_gemm_noalloc_ex(other, other.t().contiguous(), scratch_user, ca_layers=2)
+        Cn = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+        sg().sfc_gemm_noalloc_ex(dA, dB, Cn, ca_layers=0)
+        torch.cuda.synchronize()
+        assert np.array_equal(raw_bits(Cn), raw_bits(Ce)), f"noalloc {M}x{N}x{K}"
+
+
+def test_workspace_keeps_the_planned_copies():
+    """A caller's workspace, the layer count left to the library: the copies that
+    sfc_gemm_plan names are left in it and sum to C."""
+    M, N, K = 16, 4096, 8192
+    layers = sg().sfc_gemm_plan(M, N, K, 0, "auto")["layers"]
+    assert layers > 1
+    A, B = draw(M, K, ("normal", 0.0, 1.0), 9960), draw(K, N, ("normal", 0.0, 0.02), 9961)
+    C = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    ws = torch.full((16 * M * N,), float("nan"), dtype=torch.float32, device="cuda")
+    sg().sfc_gemm_ex(upload(A), upload(B), C, ca_layers=0, workspace=ws)
+    torch.cuda.synchronize()
+    copies = ws.cpu().numpy()[:layers * M * N].reshape(layers, M, N)
+    total = copies[0].copy()
+    for l in range(1, layers):
+        total += copies[l]
+    assert np.array_equal(total.view(np.uint32), raw_bits(C))
+
+
 def test_noalloc_rejects_and_leaves_c_untouched():
     M, N, K = 2049, 4096, 128
     A = upload(draw(M, K, ("uniform", -1.0, 1.0), 9901))
