@@ -1227,7 +1227,8 @@ __device__ __forceinline__ void store_tile32(const GemmParams& p, const Acc<BM, 
     for (int j = 0; j < T::FN; ++j)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        // 4 columns at element alignment; N is a multiple of 16
+        // 4 columns at element alignment, all inside C or none: calls of the fp8
+        // kernels have N a multiple of 16 (also with K = 0)
         const int64_t c = cb + j * 32 + 8 * g + 4 * h;
         const f32x16& a = acc[i][j];
         if (c >= p.N) continue;

@@ -108,6 +108,22 @@ def test_k_zero_writes_zeros(tile, out):
         assert (C == 0).all(), (tile, out, c)
 
 
+# K = 0 is accepted with any N: zeros in C and nothing beside it
+@pytest.mark.parametrize("N,ldc", [(5, 5), (5, 8), (20, 24), (20, 32), (257, 264), (257, 260)])
+@pytest.mark.parametrize("tile", ["auto", "256x256", "128x256"])
+@pytest.mark.parametrize("out", ["f32", "bf16"])
+def test_k_zero_with_any_width(N, ldc, tile, out):
+    M, guard = 3, 64
+    dtype = torch.float32 if out == "f32" else torch.bfloat16
+    buf = torch.full((M * ldc + guard,), float("nan"), dtype=dtype, device="cuda")
+    C = buf[:M * ldc].view(M, ldc)[:, :N]
+    A, B = torch.zeros((M, 16), dtype=torch.uint8, device="cuda"), torch.zeros((16, N), dtype=torch.uint8, device="cuda")
+    sg().sfc_gemm_f8_ex(A[:, :0], B[:0], C, tile=tile)
+    got = to_host(buf)
+    full = got[:M * ldc].reshape(M, ldc)
+    assert (full[:, :N] == 0).all() and np.isnan(full[:, N:]).all() and np.isnan(got[M * ldc:]).all(), (N, ldc, tile, out)
+
+
 @pytest.mark.parametrize("c", [1, 2, 5])
 def test_integer_inputs_exact(c):
     M, N, K = 300, 272, 1040
