@@ -115,6 +115,12 @@ int sfc_tile_order_ex(int gm, int gn, int order, int32_t *out_idx);
  *              hipFreeAsync on `stream`), and only work on that stream uses
  *              it, so calls on different streams may run concurrently.  It is
  *              kept, keyed by the stream handle, until the process ends.
+ *              A call recorded into a graph uses the same layers, and so gives the
+ *              same bits, as the call that runs at once; its copies and counters
+ *              lie in memory that only recorded calls of that stream use and that
+ *              is never freed, so replays may run on any stream and beside calls
+ *              that run at once.  Replays of graphs that were recorded on one
+ *              stream must not overlap each other.
  *              SFC_CA_AUTO (0): the model picks c (see sfc_gemm_model).
  *   stream     hipStream_t or NULL.
  * No GEMM entry point synchronises the device or a stream.  The first call for

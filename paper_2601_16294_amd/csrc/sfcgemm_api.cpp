@@ -31,15 +31,25 @@ struct Table {
   bool done = false;        // `ready` has been seen complete
 };
 
-// Library-owned memory of one stream: the layer copies of calls that pass no
-// workspace, and the arrival counters of fused reductions (kept zero between
-// launches).  Only work on that stream touches it, so calls on different
-// streams never share it; it grows stream-ordered.
-struct StreamMem {
+// Layer copies of calls that pass no workspace, and arrival counters of reductions
+// inside a launch.
+struct LayerMem {
   void* ws = nullptr;
   size_t ws_bytes = 0;
   int32_t* counters = nullptr;
   int64_t n_counters = 0;
+};
+
+// Library-owned memory of one stream.  Calls on different streams never share it.
+// Calls that run at once use `eager`: only work on that stream touches it, it grows
+// stream-ordered, and its counters are zero between launches.  Calls recorded into
+// a graph use `captured`: the graph keeps the addresses for its replays, so this
+// memory is never freed (a larger buffer joins the old one and is at least twice
+// its size, so all of them stay below twice the last), is no graph's own (the next
+// capture and other graphs use it too), and no replay, on whatever stream, shares
+// copies or counters with calls that run at once.
+struct StreamMem {
+  LayerMem eager, captured;
 };
 
 struct DeviceState {
@@ -118,24 +128,52 @@ int get_table(DeviceState& st, int gm, int gn, int order, hipStream_t stream, co
   return SFC_OK;
 }
 
-// At least `bytes` of layer workspace owned by `stream`.  A smaller buffer is
-// released stream-ordered (after the work already queued on the stream that
-// uses it) and a larger one allocated in stream order.  Must be called with
-// g_mu held.
+// Whether calls on `stream` are being recorded into a graph.
+bool is_captured(hipStream_t stream) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
+    (void)hipGetLastError();   // not an error: do not leave it for the next check
+    return false;
+  }
+  return cap != hipStreamCaptureStatusNone;
+}
+
+// Memory for a captured call: a plain allocation, which is refused during a capture
+// unless the thread is in the relaxed mode (an allocation in stream order would
+// become a node of the graph and its memory the graph's).
+hipError_t captured_malloc(void** out, size_t bytes) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
+  if (e != hipSuccess) return e;
+  e = hipMalloc(out, bytes);
+  const hipError_t back = hipThreadExchangeStreamCaptureMode(&mode);
+  return e != hipSuccess ? e : back;
+}
+
+// At least `bytes` of layer workspace owned by `stream`.  Outside a capture a
+// smaller buffer is released stream-ordered (after the work already queued on the
+// stream that uses it) and a larger one allocated in stream order.  Must be called
+// with g_mu held.
 int stream_workspace(DeviceState& st, hipStream_t stream, size_t bytes, void** out) {
-  StreamMem& m = st.streams[stream];
+  const bool cap = is_captured(stream);
+  LayerMem& m = cap ? st.streams[stream].captured : st.streams[stream].eager;
   if (m.ws_bytes < bytes) {
-    if (m.ws) {
-      hipError_t e = hipFreeAsync(m.ws, stream);
-      m.ws = nullptr;
-      m.ws_bytes = 0;
-      if (e != hipSuccess) return hip_fail(e, "hipFreeAsync(workspace)");
+    void* d = nullptr;
+    if (cap) {
+      if (bytes < 2 * m.ws_bytes) bytes = 2 * m.ws_bytes;
+      hipError_t e = captured_malloc(&d, bytes);
+      if (e != hipSuccess) return hip_fail(e, "hipMalloc(workspace of captured calls)");
+    } else {
+      if (m.ws) {
+        hipError_t e = hipFreeAsync(m.ws, stream);
+        m.ws = nullptr;
+        m.ws_bytes = 0;
+        if (e != hipSuccess) return hip_fail(e, "hipFreeAsync(workspace)");
+      }
+      hipError_t e = hipMallocAsync(&d, bytes, stream);
+      if (e != hipSuccess) return hip_fail(e, "hipMallocAsync(workspace)");
     }
-    hipError_t e = hipMallocAsync(&m.ws, bytes, stream);
-    if (e != hipSuccess) {
-      m.ws = nullptr;
-      return hip_fail(e, "hipMallocAsync(workspace)");
-    }
+    m.ws = d;
     m.ws_bytes = bytes;
   }
   *out = m.ws;
@@ -143,27 +181,37 @@ int stream_workspace(DeviceState& st, hipStream_t stream, size_t bytes, void** o
 }
 
 // At least n arrival counters owned by `stream`, all zero when the next
-// launch on the stream starts (new ones are cleared by a fill kernel; the
-// fused reduction leaves every counter it used at zero).  Must be called with
-// g_mu held.
+// launch on the stream starts: outside a capture new ones are cleared by a fill
+// kernel and every launch leaves those it used at zero; in a capture the fill is
+// recorded with each call.  Must be called with g_mu held.
 int stream_counters(DeviceState& st, hipStream_t stream, int64_t n, int32_t** out) {
-  StreamMem& m = st.streams[stream];
+  const bool cap = is_captured(stream);
+  LayerMem& m = cap ? st.streams[stream].captured : st.streams[stream].eager;
   if (m.n_counters < n) {
-    if (m.counters) {
-      hipError_t e = hipFreeAsync(m.counters, stream);
-      m.counters = nullptr;
-      m.n_counters = 0;
-      if (e != hipSuccess) return hip_fail(e, "hipFreeAsync(counters)");
+    void* d = nullptr;
+    int64_t count = n < 4096 ? 4096 : n;
+    if (cap) {
+      if (count < 2 * m.n_counters) count = 2 * m.n_counters;
+      hipError_t e = captured_malloc(&d, (size_t)count * 4u);
+      if (e != hipSuccess) return hip_fail(e, "hipMalloc(counters of captured calls)");
+    } else {
+      if (m.counters) {
+        hipError_t e = hipFreeAsync(m.counters, stream);
+        m.counters = nullptr;
+        m.n_counters = 0;
+        if (e != hipSuccess) return hip_fail(e, "hipFreeAsync(counters)");
+      }
+      hipError_t e = hipMallocAsync(&d, (size_t)count * 4u, stream);
+      if (e != hipSuccess) return hip_fail(e, "hipMallocAsync(counters)");
+      e = sfc::launch_fill_i32(static_cast<int32_t*>(d), count, 0, stream);
+      if (e != hipSuccess) return hip_fail(e, "counter fill");
     }
-    const int64_t cap = n < 4096 ? 4096 : n;
-    hipError_t e = hipMallocAsync(reinterpret_cast<void**>(&m.counters), (size_t)cap * 4u, stream);
-    if (e != hipSuccess) {
-      m.counters = nullptr;
-      return hip_fail(e, "hipMallocAsync(counters)");
-    }
-    e = sfc::launch_fill_i32(m.counters, cap, 0, stream);
+    m.counters = static_cast<int32_t*>(d);
+    m.n_counters = count;
+  }
+  if (cap) {
+    hipError_t e = sfc::launch_fill_i32(m.counters, n, 0, stream);
     if (e != hipSuccess) return hip_fail(e, "counter fill");
-    m.n_counters = cap;
   }
   *out = m.counters;
   return SFC_OK;
@@ -394,20 +442,9 @@ int launch_small_plan(DeviceState& st, int fm, int layers, int64_t M, int64_t N,
   p.W = W;
   p.counters = counters;
   const int64_t cells = (int64_t)p.gm * p.gn;
-  const size_t ws_bytes = (size_t)cells * (size_t)layers * (size_t)(16 * fm * 64) * 4u;
-  if (layers > 1 && !W && (st.streams[stream].ws_bytes < ws_bytes || st.streams[stream].n_counters < cells)) {
-    // memory allocated while the stream is captured would belong to the graph:
-    // one layer needs none
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
-      (void)hipGetLastError();
-      cap = hipStreamCaptureStatusNone;
-    }
-    if (cap != hipStreamCaptureStatusNone) p.layers = 1;
-  }
-  if (p.layers > 1 && !W) {
+  if (layers > 1 && !W) {
     void* own = nullptr;
-    int rc = stream_workspace(st, stream, ws_bytes, &own);
+    int rc = stream_workspace(st, stream, (size_t)cells * (size_t)layers * (size_t)(16 * fm * 64) * 4u, &own);
     if (rc == SFC_OK) rc = stream_counters(st, stream, cells, &p.counters);
     if (rc != SFC_OK) return rc;
     p.W = static_cast<float*>(own);

@@ -80,9 +80,8 @@ def test_layers_on_two_streams():
             assert np.array_equal(to_host(C), want)
 
 
-# captured into a graph on a stream without library memory (one layer then, nothing
-# is allocated) and on a stream that has it; replays beside eager work on the same
-# operands give the eager result each time
+# captured into a graph on a stream without library memory and on a stream that has
+# it; replays beside eager work on the same operands give the eager result each time
 @pytest.mark.parametrize("warm", [False, True])
 def test_graph_capture(warm):
     M, N, K = 13, 1024, 16384
@@ -107,6 +106,38 @@ def test_graph_capture(warm):
             assert np.array_equal(to_host(C), want)
             assert np.array_equal(to_host(E), want)
             E.fill_(float("nan"))
+
+
+# operands whose sums depend on their order: a recorded call has the bits of the call
+# that runs at once (and of the entry point that allocates nothing) on a cold and on a
+# warm stream, also after a call that grows the stream's memory and on another stream
+@pytest.mark.parametrize("warm", [False, True])
+def test_graph_capture_keeps_the_bits(warm):
+    M, N, K = 13, 1024, 16384
+    dA, dB = upload(draw(M, K, ("normal", 0.0, 1.0), 3910)), upload(draw(K, N, ("normal", 0.0, 1.0), 3911))
+    lA, lB = upload(draw(128, 65535, ("normal", 0.0, 1.0), 3912)), upload(draw(65535, 128, ("normal", 0.0, 1.0), 3913))
+    want, got, large = (torch.empty(s, device="cuda") for s in ((M, N), (M, N), (128, 128)))
+    sg().sfc_gemm_noalloc_ex(dA, dB, want, ca_layers=0)
+    s, t = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        if warm:
+            sg().sfc_gemm(dA, dB, got, ca_layers=0)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            sg().sfc_gemm(dA, dB, got, ca_layers=0)
+        eager = torch.empty_like(got)
+        for replay_on in (s, t, s):
+            got.fill_(float("nan"))
+            sg().sfc_gemm(lA, lB, large, ca_layers=0)
+            sg().sfc_gemm(dA, dB, eager, ca_layers=0)
+            torch.cuda.synchronize()
+            with torch.cuda.stream(replay_on):
+                g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+            assert torch.equal(eager.view(torch.int32), want.view(torch.int32))
 
 
 # infinities and NaN stay in their rows and columns (a block's neighbours, and K

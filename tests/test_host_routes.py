@@ -30,3 +30,58 @@ def test_fp8_kernels_only_see_whole_chunks(exe, M, N, ldc, tile):
         assert len(g) == 1 and g[0][0] == "gemm"
         assert g[0][1]["f8"] == 0 or N % 16 == 0, g
         assert (g[0][1]["M"], g[0][1]["N"], g[0][1]["K"]) == (M, N, 0)
+
+
+# calls that sum layer copies in library memory, and larger ones of the same kind:
+# the small-block kernel, the separate reduction, the fused one
+LAYERED = {
+    "small": (gemm("ex", 13, 1024, 16384, ca=0), gemm("ex", 128, 128, 65535, ca=0), "small"),
+    "separate": (gemm("ex", 600, 700, 4096, ca=4), gemm("ex", 1600, 1700, 4096, ca=4), "gemm"),
+    "fused": (gemm("fused", 600, 700, 4096, ca=4), gemm("fused", 16000, 17000, 4096, ca=4, tile=1), "gemm"),
+    "model": (gemm("ex", 512, 512, 32768, ca=0), gemm("ex", 1024, 1024, 65536, ca=0), "gemm"),
+}
+
+
+def memory(events, kernel):
+    e = launches(events, kernel)[0][1]
+    return {e["W"] if kernel == "small" else e["out"]} | ({e["counters"]} if e["counters"] else set())
+
+
+# a recorded call takes the layers of the call that runs at once, whether the stream
+# has library memory or not, and memory of its own that nothing frees, whatever grows
+@pytest.mark.parametrize("kind", LAYERED)
+@pytest.mark.parametrize("warm", [False, True])
+def test_captured_calls_own_their_memory(exe, kind, warm):
+    small, large, kernel = LAYERED[kind]
+    other = [c[:-1] + "2" for c in (small, large)]                    # curve tables, from another stream
+    lines = other + ([small] if warm else []) + ["capture 1 1", small, "capture 1 0", small, large, "capture 1 1", large,
+                                                 "capture 1 0", large, small]
+    calls = host_api.run(exe, lines)
+    assert all(c[-1] == ("ret", {"rc": 0}) for c in calls)
+    at = len(other) + (1 if warm else 0)
+    cap1, eager1, eager2, cap2, eager3, eager4 = (calls[at + i] for i in (1, 3, 4, 6, 8, 9))
+    for cap, eager in ((cap1, eager1), (cap2, eager2)):
+        a, b = launches(cap, kernel)[0][1], launches(eager, kernel)[0][1]
+        assert a["layers"] == b["layers"] > 1
+        assert not [e for n, e in cap if n in ("malloc_in_graph", "malloc_async", "free")]
+        # counters are zero when the launch starts: cleared in the graph itself
+        if a["counters"]:
+            names = [n for n, _ in cap]
+            assert [e["p"] for n, e in cap if n == "fill"] == [a["counters"]]
+            assert names.index("fill") < names.index(kernel)
+    held = memory(cap1, kernel) | memory(cap2, kernel)
+    for e in (eager1, eager2, eager3, eager4):
+        assert not memory(e, kernel) & held
+    assert not held & {e["p"] for c in calls for n, e in c if n == "free"}
+    if kind != "fused":    # (its larger call grows both)
+        sizes = [e["n"] for n, e in cap1 + cap2 if n == "malloc" and e["p"] in held and e["p"] != launches(cap1, kernel)[0][1]["counters"]]
+        assert len(sizes) == 2 and sizes[1] >= 2 * sizes[0]
+
+
+# an allocation that fails in a capture is reported, leaves the thread's capture mode
+# as it was (the stand-in's `capture` checks it) and the next call works
+def test_captured_allocation_failure(exe):
+    small = LAYERED["small"][0]
+    calls = host_api.run(exe, ["capture 1 1", "fail 1", small, "capture 1 0", "capture 1 1", small, "capture 1 0", small])
+    assert [c[-1][1]["rc"] for c in calls] == [0, 0, -4, 0, 0, 0, 0, 0]
+    assert not launches(calls[2])
