@@ -1256,23 +1256,28 @@ __device__ __forceinline__ void store_tile32(const GemmParams& p, const Acc<BM, 
 // them after it issues: the trailing s_nop keeps the next vector instruction
 // from overwriting them too early (the compiler inserts the same wait states
 // after its own stores).
-__device__ __forceinline__ void st16_co(void* p, u32x4 v, int co) {
-  asm volatile("s_cmp_eq_u32 %2, 0\n\t"
+__device__ __forceinline__ void st16_co(i32x4 rsrc, uint32_t off, u32x4 v, int co) {
+  asm volatile("s_cmp_eq_u32 %3, 0\n\t"
                "s_cbranch_scc1 1f\n\t"
-               "global_store_dwordx4 %0, %1, off sc1\n\t"
+               "buffer_store_dwordx4 %2, %1, %0, 0 offen sc1\n\t"
                "s_branch 2f\n"
                "1:\n\t"
-               "global_store_dwordx4 %0, %1, off\n"
+               "buffer_store_dwordx4 %2, %1, %0, 0 offen\n"
                "2:\n\t"
                "s_nop 1"
-               :: "v"(p), "v"(v), "s"(__builtin_amdgcn_readfirstlane(co)) : "memory", "scc");
+               :: "s"(rsrc), "v"(off), "v"(v), "s"(__builtin_amdgcn_readfirstlane(co)) : "memory", "scc");
 }
-// 16 bytes of an epilogue store: device scope when the kernel may fuse the
-// reduction (fp32 layer copies) and `co` is set, else a plain store.
+// 16 bytes of an epilogue store, `off` bytes into the buffer (dropped past its
+// range): device scope when the kernel may fuse the reduction (fp32 layer copies)
+// and `co` is set, else a plain store.
 template <bool FUSABLE>
-__device__ __forceinline__ void st16(void* p, u32x4 v, int co) {
-  if constexpr (FUSABLE) st16_co(p, v, co);
-  else *reinterpret_cast<u32x4*>(p) = v;
+__device__ __forceinline__ void st16(i32x4 rsrc, uint32_t off, u32x4 v, int co) {
+  if constexpr (FUSABLE) {
+    st16_co(rsrc, off, v, co);
+  } else {
+    void* base = reinterpret_cast<void*>((uint64_t)(uint32_t)rsrc[0] | ((uint64_t)(uint32_t)rsrc[1] << 32));
+    __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(base, 0, rsrc[2], rsrc[3]), (int)off, 0, 0);
+  }
 }
 __device__ __forceinline__ void st_f32(float* p, float v, int co) {
   if (co) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1287,15 +1292,21 @@ __device__ __forceinline__ void st_f32(float* p, float v, int co) {
 // instruction then covers 1024 / (row bytes) whole row segments instead of 16
 // or 32 rows of 32-64 bytes, and the store path issues it faster (measured on
 // MI355X: about a third less time for the block's stores).  16-byte aligned rows
-// of C only; edge blocks store the 16-byte pieces that lie inside C (their
-// operands' N is a multiple of 8 bf16 or 16 fp8 elements, so a piece is all in or
-// all out).  Edge blocks stored element by element took longer than the rest of
-// a short-K grid: 5824x2304x184 bf16 out 33.1 -> 15.5 us, 1984x4608x64 f32 31.9 ->
-// 16.4, 2029x7280x624 fp8 44.5 -> 18.8, 1204x1784x2128 f32 27.5 -> 23.2.  The checks are a
-// copy of the store loop of their own (in the interior blocks' loop they cost 1 %
-// on 8192x4096x512).  A sub-block that does not fit the rings at once goes in
-// several row passes.  The caller synchronises the workgroup
-// before the rings are written again.
+// of C only; the stores go through a buffer descriptor whose range ends with the
+// rows inside C, lanes right of C point past it, so one loop without checks serves
+// interior and edge blocks (a 16-byte piece is all in or all out: the operands' N is
+// a multiple of 8 bf16 or 16 fp8 elements).  A copy of the loop for edge blocks cost
+// the interior ones 1-2 % on short K (8192x4096x512 bf16 out: 41.6 us against 40.9,
+// 4097x4096x512 33.1 against 32.5).  Passes with fewer rows run a rolled loop over
+// those rows and write only the first 32 rows to LDS where no more are inside: one row
+// of 4160 columns, K 256, takes 6.8-9.4 us with the 128- and 256-row blocks; the
+// whole sub-block through LDS took 7.9-11.3, and element stores, whose time grows
+// with the rows, 7.6-10.2 (127 rows: 21.6-24.0, here 8.0-10.4).  Other edges, element
+// stores -> here: 5824x2304x184 bf16 out 32.9 -> 14.5, 1984x4608x64 f32 32.0 -> 16.0,
+// 2029x7280x624 fp8 bf16 out 43.4 -> 17.7, 1204x1784x2128 f32 27.0 -> 22.0.  A sub-block
+// that does not fit the rings at once goes in several row passes.  The caller
+// synchronises the workgroup before the rings are written again.
+constexpr int64_t kMaxStagedLdo = (int64_t)1 << 22;   // byte offsets within a sub-block stay below 2^31
 template <int BM, int BN, int NW, int F8, bool OUT_BF16>
 struct Staging {
   using T = Tile<BM, BN, NW, F8>;
@@ -1328,7 +1339,7 @@ __device__ __forceinline__ u32x4 lds_read16(uint32_t addr) {
 template <int BM, int BN, int NW, int F8, bool OUT_BF16>
 __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const Acc<BM, BN, NW, F8>& acc, int64_t m0,
                                                   int64_t n0, int64_t lstride, int wm, int wn, int wave, int lane,
-                                                  uint32_t lds0, int co, bool interior) {
+                                                  uint32_t lds0, int co) {
   using T = Tile<BM, BN, NW, F8>;
   using S = Staging<BM, BN, NW, F8, OUT_BF16>;
   typedef typename std::conditional<OUT_BF16, __bf16, float>::type OutT;
@@ -1336,8 +1347,13 @@ __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const Acc
   OutT* out = reinterpret_cast<OutT*>(p.out) + lstride;
   const uint32_t base = lds0 + (uint32_t)(wave * S::PASS_ROWS * S::RS);
   const int64_t row0 = m0 + wm * T::WTM, col0 = n0 + wn * T::WTN;
+  const uint32_t row_bytes = (uint32_t)p.ldo * S::ES;
 #pragma unroll
   for (int pass = 0; pass < S::PASSES; ++pass) {
+    // rows of this pass inside C
+    const int64_t left = p.M - (row0 + pass * S::PASS_ROWS);
+    int rows = __builtin_amdgcn_readfirstlane((int)(left < 0 ? 0 : left < S::PASS_ROWS ? left : S::PASS_ROWS));
+    pin_scalar(rows);
     // fragments of sub-block rows [pass*PASS_ROWS, +PASS_ROWS) into LDS
     if constexpr (F8 != 0) {
       // 32x32 fragments: lane l, run g: row 32i + l%32, columns 32j + 8g + 4(l/32)
@@ -1345,6 +1361,7 @@ __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const Acc
 #pragma unroll
       for (int ii = 0; ii < S::PASS_ROWS / 32; ++ii) {
         const int i = pass * (S::PASS_ROWS / 32) + ii;
+        if (ii == 1 && rows <= 32) break;
         const uint32_t rowa = base + (uint32_t)((32 * ii + r) * S::RS);
 #pragma unroll
         for (int j = 0; j < T::FN; ++j) {
@@ -1374,6 +1391,7 @@ __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const Acc
 #pragma unroll
       for (int ii = 0; ii < S::PASS_ROWS / 16; ++ii) {
         const int i = pass * (S::PASS_ROWS / 16) + ii;
+        if (ii == 2 && rows <= 32) break;
         const uint32_t rowa = base + (uint32_t)((16 * ii + r) * S::RS);
         if constexpr (OUT_BF16) {
 #pragma unroll
@@ -1388,26 +1406,43 @@ __device__ __forceinline__ void store_tile_staged(const GemmParams& p, const Acc
       }
     }
     wait_lds_all();
-    // whole row segments back out: lane l reads chunk l % CPR of row l / CPR
+    // whole row segments back out: lane l reads chunk l % CPR of row l / CPR; chunks
+    // outside C lie past the buffer's range
     const int rr = lane / S::CPR, cc = lane % S::CPR;
-    auto rows_out = [&](auto edge) {
+    const i32x4 rsrc = make_rsrc_addr(reinterpret_cast<uint64_t>(out + (row0 + pass * S::PASS_ROWS) * p.ldo + col0),
+                                      (uint32_t)rows * row_bytes);
+    uint32_t off = col0 + cc * (16 / S::ES) < p.N ? (uint32_t)rr * row_bytes + (uint32_t)(cc * 16) : 0x80000000u;
+    uint32_t src = base + (uint32_t)(rr * S::RS + cc * 16);
+    const uint32_t step = S::RPI * row_bytes;
+    if (__builtin_expect(rows == S::PASS_ROWS, 1)) {
 #pragma unroll
       for (int t = 0; t < S::PASS_ROWS / S::RPI; t += 4) {
         u32x4 v[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-          if (t + u < S::PASS_ROWS / S::RPI) v[u] = lds_read16(base + (uint32_t)(((t + u) * S::RPI + rr) * S::RS + cc * 16));
+          if (t + u < S::PASS_ROWS / S::RPI) v[u] = lds_read16(src + (uint32_t)((t + u) * S::RPI * S::RS));
 #pragma unroll
         for (int u = 0; u < 4; ++u)
           if (t + u < S::PASS_ROWS / S::RPI) {
-            const int64_t row = row0 + pass * S::PASS_ROWS + (t + u) * S::RPI + rr;
-            if (!decltype(edge)::value || (row < p.M && col0 + cc * (16 / S::ES) < p.N))
-              st16<!OUT_BF16 && F8 == 0>(out + row * p.ldo + col0 + cc * (16 / S::ES), v[u], co);
+            st16<!OUT_BF16 && F8 == 0>(rsrc, off, v[u], co);
+            off += step;
           }
       }
-    };
-    if (interior) rows_out(std::false_type{});
-    else rows_out(std::true_type{});
+    } else {
+      constexpr int U = S::PASS_ROWS / S::RPI < 4 ? S::PASS_ROWS / S::RPI : 4;
+#pragma unroll 1
+      for (int r = 0; r < rows; r += U * S::RPI) {
+        u32x4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = lds_read16(src + (uint32_t)(u * S::RPI * S::RS));
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          st16<!OUT_BF16 && F8 == 0>(rsrc, off, v[u], co);
+          off += step;
+        }
+        src += U * S::RPI * S::RS;
+      }
+    }
     if (pass + 1 < S::PASSES) wait_lds_all();   // this wave's reads are done before its next writes
   }
 }
@@ -1512,6 +1547,7 @@ __device__ __forceinline__ void store_tile_any(const GemmParams& p, const Acc<BM
   const int64_t c0 = n0 + wn * T::WTN + (OUT_BF16 ? 16 * (q & 1) + 8 * (q >> 1) : 4 * q);
 #pragma unroll
   for (int i = 0; i < T::FM; ++i) {
+    if (m0 + wm * T::WTM + 16 * i >= p.M) break;   // (wave-uniform; 1 row, 256x256 blocks: 14.4 -> 9.5 us)
     const int64_t r = r0 + i * 16;
     OutT* row = out + r * p.ldo + c0;
 #pragma unroll
@@ -1757,12 +1793,13 @@ __global__ __launch_bounds__(NW * 64, 1) void sfc_gemm_kernel(GemmParams p) {
     const bool fused = kFusable && e.counters != nullptr;
     // kernels whose aligned blocks all leave through LDS keep the plain element
     // stores for unaligned rows of C: the 16-byte form beside them made the register
-    // allocator move accumulators inside the K loop (f32 128x256: +25 % time)
+    // allocator move accumulators inside the K loop (measured on f32 128x256, +25 %
+    // time; the others follow it)
     constexpr bool kStoreAny = F8 == 0 && (LOADS == kLoadAny || (LOADS == kLoadRing && !Staging<BM, BN, NW, F8, OUT_BF16>::USE));
-    if (LOADS == kLoadRing && Staging<BM, BN, NW, F8, OUT_BF16>::USE && (OUT_BF16 ? vec16_store : vec_store)) {
+    if (LOADS == kLoadRing && Staging<BM, BN, NW, F8, OUT_BF16>::USE && (OUT_BF16 ? vec16_store : vec_store) && e.ldo < kMaxStagedLdo) {
       if constexpr (LOADS == kLoadRing && Staging<BM, BN, NW, F8, OUT_BF16>::USE) {
         store_tile_staged<BM, BN, NW, F8, OUT_BF16>(e, acc, m0, n0, lstride, wm, wn, wave, lane_t, lds_addr(smem),
-                                                    fused ? 1 : 0, interior);
+                                                    fused ? 1 : 0);
         // every wave has read its staging rows before the next task's loads
         // land in the rings
         wait_lds_all();

@@ -84,3 +84,37 @@ def test_edge_blocks_of_aligned_operands(M, N, tile):
     for out, pad in (("f32", 4), ("bf16", 8), ("f32", 1), ("bf16", 3)):
         check(M, N, 136, tile, 1, out, 136, N, N + pad, 2700 + M)
     check(M, N, 136, tile, 2, "f32", 136, N + 8, N, 2800 + M)
+
+
+# leading dimensions of C around the limit of the edge stores' 32-bit offsets: rows
+# inside C only, nothing right of C
+@pytest.mark.parametrize("out", ["f32", "bf16"])
+@pytest.mark.parametrize("ldc", [(1 << 22) - 8, 1 << 22])
+def test_wide_rows_of_c(out, ldc):
+    M, N, K = 131, 264, 72
+    A, B = draw(M, K, ("int", -4, 4), 2900), draw(K, N, ("int", -4, 4), 2901)
+    want = (obf16.bf16_to_f64(A) @ obf16.bf16_to_f64(B)).astype(np.float32)
+    if out == "bf16":
+        want = obf16.bf16_to_f64(obf16.f32_to_bf16_rne(want))
+    C = torch.empty((M, ldc), dtype=torch.float32 if out == "f32" else torch.bfloat16, device="cuda")
+    for tile in TILES:
+        C[:, :N + 64] = float("nan")
+        C[:, -64:] = float("nan")
+        sg().sfc_gemm_ex(upload(A), upload(B), C[:, :N], tile=tile)
+        assert np.array_equal(to_host(C[:, :N]), want.astype(np.float64)), tile
+        assert torch.isnan(C[:, N:N + 64]).all() and torch.isnan(C[:, -64:]).all(), tile
+
+
+# few rows in the last row of blocks, and layer copies (stored at device scope when
+# the launch sums them itself)
+@pytest.mark.parametrize("M", [1, 31, 32, 33, 129, 160, 161, 257, 290])
+@pytest.mark.parametrize("tile", TILES)
+def test_few_rows_in_the_last_blocks(M, tile):
+    N, K = 328, 136
+    for out in ("f32", "bf16"):
+        check(M, N, K, tile, 1, out, K, N, N + 8, 2910 + M)
+    A, B = draw(M, K, ("int", -4, 4), 2920), draw(K, N, ("int", -4, 4), 2921)
+    C = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    sg().sfc_gemm_fused_ex(upload(A), upload(B), C, ca_layers=3, tile=tile)
+    want = obf16.bf16_to_f64(A) @ obf16.bf16_to_f64(B)
+    assert np.array_equal(to_host(C), want)

@@ -124,6 +124,22 @@ def test_k_zero_with_any_width(N, ldc, tile, out):
     assert (full[:, :N] == 0).all() and np.isnan(full[:, N:]).all() and np.isnan(got[M * ldc:]).all(), (N, ldc, tile, out)
 
 
+# few rows in the last row of blocks and a last block column that ends inside a wave's
+# columns: exact sums inside C, nothing beside it
+@pytest.mark.parametrize("M", [1, 31, 32, 33, 65, 129, 161, 257, 300])
+@pytest.mark.parametrize("tile", ["256x256", "128x256"])
+@pytest.mark.parametrize("out", ["f32", "bf16"])
+def test_edge_rows_and_columns(M, tile, out):
+    N, K = 336, 144
+    A, B = draw_e4m3(M, K, ("int", -4, 4), 41), draw_e4m3(K, N, ("int", -4, 4), 42)
+    want = (of8.e4m3_to_f64(A) @ of8.e4m3_to_f64(B)).astype(np.float32)
+    if out == "bf16":
+        want = obf16.bf16_to_f64(obf16.f32_to_bf16_rne(want))
+    for ldc in (N + 16, N + 3):
+        C = to_host(run8(A, B, M, N, K, out, 1, ldc, tile=tile))
+        assert np.array_equal(C[:, :N], want.astype(np.float64)) and np.isnan(C[:, N:]).all(), ldc
+
+
 @pytest.mark.parametrize("c", [1, 2, 5])
 def test_integer_inputs_exact(c):
     M, N, K = 300, 272, 1040
