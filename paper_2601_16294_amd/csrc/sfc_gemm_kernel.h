@@ -1779,7 +1779,10 @@ __global__ __launch_bounds__(NW * 64, 1) void sfc_gemm_kernel(GemmParams p) {
       if (tail) any_tail<BM, BN, NW>(p, smem, m0, n0, kt1 - 1, tid, acc);
     }
 
-    const GemmParams e = reload_params();
+    // (the 256x256 kernel with bf16 output parks no scalars in its K loop and would only
+    // wait for the loads, twice on 4097x4096x512: 34.0 us with them, 33.6 without)
+    constexpr bool kReload = !(BM == 256 && BN == 256 && F8 == 0 && OUT_BF16 && LOADS == kLoadRing);
+    const GemmParams e = kReload ? reload_params() : p;
     // 4-wide stores need 4-element aligned rows (and layer copies).
     const int esize = OUT_BF16 ? 2 : 4;
     const bool vec_store = ((uintptr_t)e.out % (4 * esize)) == 0 && (e.ldo % 4) == 0 &&
