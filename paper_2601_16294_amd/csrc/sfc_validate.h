@@ -111,6 +111,19 @@ inline int strip_columns(int gm, int gn, int64_t slots, int64_t half_rows, int64
   return (int)w;
 }
 
+// The strip of an M x N output cut into bm x bn blocks (bm = 256): strip_columns, and
+// none if fewer than `min_cols` columns would be its own.
+inline int strip_width(int64_t M, int64_t N, int bm, int bn, int64_t slots, int64_t half_slots, int64_t min_cols) {
+  const int64_t gm = ceil_div(M, bm), gn = ceil_div(N, bn);
+  if (gm * gn >= ((int64_t)1 << 30)) return 0;
+  const int w = strip_columns((int)gm, (int)gn, slots, ceil_div(M, bm / 2), half_slots);
+  return w > 0 && N - (gn - w) * bn >= min_cols ? w : 0;
+}
+
+// Columns that a launch needs at least: at any alignment a row's last chunk is
+// loaded from 8 elements before its end.
+inline int64_t min_columns(bool any_alignment) { return any_alignment ? 8 : 1; }
+
 // Whether a launch takes the 4-deep ring of 128x128 blocks: the fast path,
 // bf16 operands, 128x128 blocks and no more tasks (blocks x layers) than CUs,
 // so that one workgroup per CU (instead of two) loses nothing.

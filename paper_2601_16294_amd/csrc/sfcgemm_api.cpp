@@ -306,7 +306,8 @@ int make_plan(DeviceState& st, int64_t M, int64_t N, int64_t K, const void* A, i
         sfc::model_choose(M, N, K, ob ? 2 : 4, st.num_cus, occ,
                           tile_api == SFC_TILE_AUTO ? -1 : tile_from_api(tile_api), ca_layers);
     if (tile_api == SFC_TILE_AUTO && pl->loads != sfc::kLoadElements &&
-        sfc::strip_beats_128x256(M, N, sfc::ceil_div(K, sfc::kBK), ob ? 2 : 4, st.num_cus, ch))
+        sfc::strip_beats_128x256(M, N, sfc::ceil_div(K, sfc::kBK), ob ? 2 : 4, st.num_cus, ch,
+                                 sfc::min_columns(pl->loads == sfc::kLoadAny)))
       ch.tile = sfc::kT256x256;
     pl->tile = ch.tile;
     pl->ce = sfc::effective_layers(K, ch.layers, sfc::kBK);
@@ -355,24 +356,21 @@ int plan_tail_split(DeviceState& st, const Plan& pl, int64_t M, int64_t N, int64
   int occ2 = 1;
   int rc = get_occupancy(st, {half, ob, pl.loads, f8}, &occ2);
   if (rc != SFC_OK) return rc;
-  const int64_t half_rows = sfc::ceil_div(M, sfc::tile_bm(half));
-  const int w = sfc::strip_columns(pl.gm, pl.gn, (int64_t)st.num_cus * pl.occ, half_rows,
-                                   (int64_t)st.num_cus * occ2);
+  const int w = sfc::strip_width(M, N, pl.bm, pl.bn, (int64_t)st.num_cus * pl.occ, (int64_t)st.num_cus * occ2,
+                                 sfc::min_columns(pl.loads == sfc::kLoadAny));
   if (w == 0) return SFC_OK;
   Plan& q = sp->strip;
   q.tile = half;
   q.bm = sfc::tile_bm(half);
   q.bn = sfc::tile_bn(half);
   const int64_t n1 = (int64_t)(pl.gn - w) * pl.bn;
-  q.gm = (int)half_rows;
+  q.gm = (int)sfc::ceil_div(M, q.bm);
   q.gn = (int)sfc::ceil_div(N - n1, q.bn);
   q.ce = 1;
   q.nk = pl.nk;
   q.occ = occ2;
-  // n1 is a multiple of 128, so the strip's B is aligned as B is, and its last
-  // columns need 8 elements of their own only at any alignment
+  // n1 is a multiple of 128, so the strip's B is aligned as B is
   q.loads = pl.loads;
-  if (pl.loads == sfc::kLoadAny && !sfc::any_loads_ok(lda, ldb, K, N - n1)) return SFC_OK;
   q.grid = (int)((int64_t)q.gm * q.gn);
   sp->w = w;
   sp->on = true;

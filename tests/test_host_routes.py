@@ -85,3 +85,22 @@ def test_captured_allocation_failure(exe):
     calls = host_api.run(exe, ["capture 1 1", "fail 1", small, "capture 1 0", "capture 1 1", small, "capture 1 0", small])
     assert [c[-1][1]["rc"] for c in calls] == [0, 0, -4, 0, 0, 0, 0, 0]
     assert not launches(calls[2])
+
+
+def model_shape(M, N, K, out):
+    """The model's block shape (SFC_TILE_*, layers) with one layer, at the kernels' occupancy."""
+    from paper_2601_16294_amd import sfcgemm as sg
+    return sg.sfc_gemm_model(M, N, K, out="bf16" if out else "f32", ca_layers=1)["tile"]
+
+
+# 256x256 blocks take over from the model's 128x256 blocks only together with the
+# half-height strip (unaligned operands: a strip of fewer than 8 columns is refused)
+@pytest.mark.parametrize("M,N,K", [(2468, 13057, 4096), (2468, 13063, 4096), (2468, 13064, 4096), (2468, 13056 + 255, 4096),
+                                   (1300, 14337, 4096), (1300, 14345, 4096), (2561, 8001, 4099), (2561, 7937, 4099)])
+def test_whole_blocks_only_with_their_strip(exe, M, N, K):
+    for out in (0, 1):
+        assert model_shape(M, N, K, out) == "128x256"
+        g = [e for _, e in launches(host_api.run(exe, [gemm("ex", M, N, K, out)])[0])]
+        tiles = [e["tile"] for e in g]
+        assert tiles in ([2], [3, 2]), tiles
+        assert sum(e["N"] for e in g) == N and all(e["N"] >= 8 for e in g)
