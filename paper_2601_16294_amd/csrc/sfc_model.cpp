@@ -81,10 +81,10 @@ ModelChoice model_choose(int64_t M, int64_t N, int64_t K, int out_bytes, int num
 }
 
 bool strip_beats_128x256(int64_t M, int64_t N, int64_t nk, int out_bytes, int num_cus, const ModelChoice& ch,
-                         int64_t min_cols, const ModelConst& k) {
+                         int64_t min_cols, bool f8, const ModelConst& k) {
   if (ch.tile != kT128x256 || ch.layers != 1) return false;
   const int64_t gm = cdiv(M, 256), gn = cdiv(N, 256);
-  const int w = strip_width(M, N, 256, 256, num_cus, num_cus, min_cols);
+  const int w = strip_width(M, N, 256, 256, num_cus, num_cus, min_cols, f8 ? nk : 0);
   if (w == 0) return false;
   const int64_t full = gm * gn / num_cus, left = gm * gn % num_cus;
   if (full < 2 && 4 * left < num_cus) return false;

@@ -53,10 +53,10 @@ ModelChoice model_choose(int64_t M, int64_t N, int64_t K, int out_bytes, int num
 // f32 291 -> 265, fp8 153 -> 141; 5120x4096x8192 bf16 307 -> 277; 1300x14336x4096 160 ->
 // 149; 3001x7003x5001 313 -> 259; 5500x4096x4096 171 -> 168.  Where the rule says no:
 // 3000x7000x2048 89 -> 99, 2800x6144x4096 153 -> 180, 3300x6144x4096 164 -> 182.
-// min_cols: what the strip's launch needs (min_columns); without a strip the model's
-// choice stands.
+// min_cols: what the strip's launch needs (min_columns); f8: nk counts the K blocks of
+// fp8 operands.  Without a strip the model's choice stands.
 bool strip_beats_128x256(int64_t M, int64_t N, int64_t nk, int out_bytes, int num_cus, const ModelChoice& ch,
-                         int64_t min_cols = 1, const ModelConst& k = ModelConst());
+                         int64_t min_cols = 1, bool f8 = false, const ModelConst& k = ModelConst());
 
 // The small-block kernel (sfc_small.hip): blocks of 16*fm rows x 64 columns, `layers`
 // ranges of K, every block and layer in flight at once (at most one per CU).

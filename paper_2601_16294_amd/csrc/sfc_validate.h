@@ -111,11 +111,29 @@ inline int strip_columns(int gm, int gn, int64_t slots, int64_t half_rows, int64
   return (int)w;
 }
 
+// Whether an fp8 call of `nk` 128-deep K blocks gains from a strip in place of a last
+// round of `left` blocks after `full` whole rounds.  An fp8 block takes half the time of
+// a bf16 one, and a part-filled round runs at a higher clock, so the strip's launch
+// (3-6 us) weighs more.  Timed against one launch of 256x256 blocks, 4096 rows, bf16 out,
+// several boxes (time of the one launch over that with the strip):
+//   2 rounds + 1/8 .. 1/2: K 3072-4096 1.02-1.11 (K 2048-2560: the model's 128x256 blocks);
+//   3 rounds + 3/16 .. 7/16: K 2048-4096 1.01-1.05, 8192 1.06; K 256-1024 0.97-1.01;
+//   3 rounds + 1/2: K 4096-8192 1.00-1.03, 3072 0.99-1.00, 2048 0.99-1.04, 256-512 0.96-0.97;
+//   3 rounds + 1/16, 1/8: K 8192 1.02, 4096 0.99-1.02, 2048 0.97-1.01, 256-1024 0.95-0.99;
+//   4 or 6 rounds + 1/8: K 2048 0.98-0.99, 256-1024 0.90-0.94; 5 + 1/4: K 8192 1.01.
+inline bool f8_strip_pays(int64_t nk, int64_t full, int64_t left, int64_t slots) {
+  if (full <= 2) return nk >= 24;
+  return nk >= (16 * left < 3 * slots ? 64 : 16 * left > 7 * slots ? 32 : 16);
+}
+
 // The strip of an M x N output cut into bm x bn blocks (bm = 256): strip_columns, and
-// none if fewer than `min_cols` columns would be its own.
-inline int strip_width(int64_t M, int64_t N, int bm, int bn, int64_t slots, int64_t half_slots, int64_t min_cols) {
+// none if fewer than `min_cols` columns would be its own, or where it does not pay for
+// fp8 operands (f8_blocks: their 128-deep K blocks; 0: bf16 operands).
+inline int strip_width(int64_t M, int64_t N, int bm, int bn, int64_t slots, int64_t half_slots, int64_t min_cols,
+                       int64_t f8_blocks) {
   const int64_t gm = ceil_div(M, bm), gn = ceil_div(N, bn);
-  if (gm * gn >= ((int64_t)1 << 30)) return 0;
+  if (gm * gn >= ((int64_t)1 << 30) || slots < 1) return 0;
+  if (f8_blocks > 0 && !f8_strip_pays(f8_blocks, gm * gn / slots, gm * gn % slots, slots)) return 0;
   const int w = strip_columns((int)gm, (int)gn, slots, ceil_div(M, bm / 2), half_slots);
   return w > 0 && N - (gn - w) * bn >= min_cols ? w : 0;
 }

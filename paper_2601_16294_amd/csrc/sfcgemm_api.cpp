@@ -272,7 +272,7 @@ int make_plan(DeviceState& st, int64_t M, int64_t N, int64_t K, const void* A, i
         const sfc::ModelChoice ch = sfc::model_choose(M, N, k_equiv, ob ? 2 : 4, st.num_cus, occ, t, ca_layers);
         if (best.tile < 0 || ch.clk < best.clk) best = ch;
       }
-      if (tile < 0 && sfc::strip_beats_128x256(M, N, k_equiv / sfc::kBK, ob ? 2 : 4, st.num_cus, best))
+      if (tile < 0 && sfc::strip_beats_128x256(M, N, k_equiv / sfc::kBK, ob ? 2 : 4, st.num_cus, best, 1, true))
         best.tile = sfc::kT256x256;
       tile = best.tile;
       layers = best.layers;
@@ -357,7 +357,7 @@ int plan_tail_split(DeviceState& st, const Plan& pl, int64_t M, int64_t N, int64
   int rc = get_occupancy(st, {half, ob, pl.loads, f8}, &occ2);
   if (rc != SFC_OK) return rc;
   const int w = sfc::strip_width(M, N, pl.bm, pl.bn, (int64_t)st.num_cus * pl.occ, (int64_t)st.num_cus * occ2,
-                                 sfc::min_columns(pl.loads == sfc::kLoadAny));
+                                 sfc::min_columns(pl.loads == sfc::kLoadAny), f8 ? pl.nk : 0);
   if (w == 0) return SFC_OK;
   Plan& q = sp->strip;
   q.tile = half;

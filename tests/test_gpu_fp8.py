@@ -223,10 +223,14 @@ def test_auto_layers(M, N, K):
 
 
 # a partial last round of 256x256 blocks leaves its last block columns to
-# half-height blocks of their own launch (SFC_TILE_AUTO): same bits as whole blocks
+# half-height blocks of their own launch (SFC_TILE_AUTO) where K is deep enough for
+# that (not the first two): same bits as whole blocks
 @pytest.mark.parametrize("M,N,K,out,fa,fb", [(4000, 256 * 52 - 240, 400, "f32", "e4m3", "e4m3"),
                                              (4096, 256 * 56, 128, "bf16", "e5m2", "e4m3"),
-                                             (1300, 14336, 8192, "bf16", "e4m3", "e4m3")])
+                                             (1300, 14336, 8192, "bf16", "e4m3", "e4m3"),
+                                             (4000, 256 * 52 - 240, 2064, "f32", "e4m3", "e5m2"),
+                                             (4096, 256 * 56, 4096, "bf16", "e5m2", "e4m3"),
+                                             (4001, 9232, 3088, "f32", "e4m3", "e4m3")])
 def test_half_height_strip(M, N, K, out, fa, fb):
     A = draw_fp8(M, K, ("normal", 0.0, 1.0), 9101, fmt=fa)
     B = draw_fp8(K, N, ("normal", 0.0, 1.0), 9102, fmt=fb)

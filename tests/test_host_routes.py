@@ -104,3 +104,29 @@ def test_whole_blocks_only_with_their_strip(exe, M, N, K):
         tiles = [e["tile"] for e in g]
         assert tiles in ([2], [3, 2]), tiles
         assert sum(e["N"] for e in g) == N and all(e["N"] >= 8 for e in g)
+
+
+# the strip of fp8 calls, by full rounds, remainder and depth: taken where it gains on
+# every box that timed it, else one launch
+@pytest.mark.parametrize("rounds,K,strip", [
+    ((3, 8), 4096, True), ((3, 8), 8192, True), ((3, 8), 3072, False), ((3, 8), 512, False),
+    ((3, 4), 4096, True), ((3, 4), 2048, True), ((3, 4), 1024, False), ((3, 4), 256, False),
+    ((3, 2), 8192, True), ((3, 2), 4096, False), ((3, 1), 2048, False), ((4, 2), 1024, False),
+    ((2, 4), 4096, True), ((2, 8), 3072, True), ((3, 12), 4096, False), ((4, 0), 4096, False)])
+def test_fp8_strip(exe, rounds, K, strip):
+    M, N = 4096, 256 * (16 * rounds[0] + rounds[1])
+    for out in (0, 1):
+        g = [e for _, e in launches(host_api.run(exe, [gemm("f8", M, N, K, out)])[0])]
+        assert [e["tile"] for e in g] == ([3, 2] if strip else [3]), (rounds, K, out)
+        assert sum(e["N"] for e in g) == N and all(e["f8"] == 1 for e in g)
+
+
+# no strip without the 256x256 blocks it belongs to: a short fp8 call keeps the shape of
+# the model where the strip would not pay
+def test_fp8_shape_without_a_strip(exe):
+    for K in (1024, 2048):
+        for w in range(1, 17):
+            for R in (1, 2):
+                M, N = 4096, 256 * (16 * R + w)
+                g = [e["tile"] for _, e in launches(host_api.run(exe, [gemm("f8", M, N, K, 1)])[0])]
+                assert len(g) == 1
