@@ -96,24 +96,19 @@ __device__ __forceinline__ int b_off(int k, int n) {
 }
 
 // ---- global -> register staging -------------------------------------------------
-template <bool VEC>
+// 8 elements of a row, one by one (zeros outside the matrix).
 __device__ __forceinline__ u32x4 load_chunk(const uint16_t* base, int64_t ld, int64_t row,
                                             int64_t col, int64_t rows, int64_t cols) {
   u32x4 v = {0u, 0u, 0u, 0u};
-  if (VEC) {
-    // cols is a multiple of 8 and rows are 16-byte aligned: a chunk is all in or all out.
-    if (row < rows && col < cols) v = *reinterpret_cast<const u32x4*>(base + row * ld + col);
-  } else {
-    if (row < rows) {
-      const uint16_t* p = base + row * ld;
-      uint32_t w[4] = {0u, 0u, 0u, 0u};
+  if (row < rows) {
+    const uint16_t* p = base + row * ld;
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const uint32_t h = (col + e < cols) ? (uint32_t)p[col + e] : 0u;
-        w[e >> 1] |= h << ((e & 1) * 16);
-      }
-      v[0] = w[0]; v[1] = w[1]; v[2] = w[2]; v[3] = w[3];
+    for (int e = 0; e < 8; ++e) {
+      const uint32_t h = (col + e < cols) ? (uint32_t)p[col + e] : 0u;
+      w[e >> 1] |= h << ((e & 1) * 16);
     }
+    v[0] = w[0]; v[1] = w[1]; v[2] = w[2]; v[3] = w[3];
   }
   return v;
 }
@@ -1004,12 +999,12 @@ __device__ __forceinline__ void main_loop_staged(const GemmParams& p, uint16_t* 
 #pragma unroll
     for (int i = 0; i < T::A_CH; ++i) {
       const int q = tid + T::THREADS * i;
-      ra[i] = load_chunk<false>(p.A, p.lda, m0 + (q >> 3), k0 + (q & 7) * 8, p.M, p.K);
+      ra[i] = load_chunk(p.A, p.lda, m0 + (q >> 3), k0 + (q & 7) * 8, p.M, p.K);
     }
 #pragma unroll
     for (int i = 0; i < T::B_CH; ++i) {
       const int q = tid + T::THREADS * i;
-      rb[i] = load_chunk<false>(p.B, p.ldb, k0 + q / (BN / 8), n0 + (q % (BN / 8)) * 8, p.K, p.N);
+      rb[i] = load_chunk(p.B, p.ldb, k0 + q / (BN / 8), n0 + (q % (BN / 8)) * 8, p.K, p.N);
     }
   };
   auto store_blocks = [&](int buf) {

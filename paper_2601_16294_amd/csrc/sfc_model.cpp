@@ -104,7 +104,7 @@ bool strip_beats_128x256(int64_t M, int64_t N, int64_t nk, int out_bytes, int nu
 // (128-byte row segments of B; the curve kernel's 512-byte ones reach 6.0); with
 // several layers 2.2 us for the count's round trip and the last workgroup's read
 // of a block's copies at about 30 bytes per ns.
-SmallChoice small_choose(int64_t M, int64_t N, int64_t K, int out_bytes, int num_cus, int ca_layers, bool layers_ok) {
+SmallChoice small_choose(int64_t M, int64_t N, int64_t K, int out_bytes, int num_cus, int ca_layers) {
   SmallChoice best{0, 1, 1e300};
   // more blocks than CUs of the tallest shape (a second round of workgroups would
   // cost more than the curve kernel's larger blocks)
@@ -122,7 +122,7 @@ SmallChoice small_choose(int64_t M, int64_t N, int64_t K, int out_bytes, int num
     const int fm = 1 << i;
     const int64_t tiles = cdiv(M, 16 * fm) * cdiv(N, 64);
     // layers only where the curve kernel would use them too
-    const int max_layers = layers_ok && ca_layers == 0 && old.layers > 1 ? kModelMaxLayers : 1;
+    const int max_layers = ca_layers == 0 && old.layers > 1 ? kModelMaxLayers : 1;
     for (int c = 1; c <= max_layers && tiles * c <= num_cus; c *= 2) {
       if (c > 1 && nk < 8 * c) break;               // at least two stages per wave
       const double rounds = (double)cdiv(nk, 4 * c);

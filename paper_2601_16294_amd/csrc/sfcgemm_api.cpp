@@ -345,8 +345,7 @@ struct Split {
   Plan strip;     // the strip's plan (half-height blocks)
 };
 
-int plan_tail_split(DeviceState& st, const Plan& pl, int64_t M, int64_t N, int64_t K, const void* A,
-                    int64_t lda, const void* B, int64_t ldb, bool ob, int f8, Split* sp) {
+int plan_tail_split(DeviceState& st, const Plan& pl, int64_t M, int64_t N, bool ob, int f8, Split* sp) {
   sp->on = false;
   if (pl.ce != 1 || pl.loads == sfc::kLoadElements) return SFC_OK;
   int half;
@@ -414,10 +413,10 @@ int launch_plan(const Plan& pl, const int32_t* table, int64_t M, int64_t N, int6
 // Whether a call whose block shape is the library's to choose runs on the
 // small-block kernel (fm = 0: no), and how.
 sfc::SmallChoice small_choice(const DeviceState& st, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool ob,
-                              int ca_layers, bool layers_ok) {
+                              int ca_layers) {
   // (K well inside 32 bits: the kernel's K indices run up to a stage past it)
   if (ca_layers > 1 || K > ((int64_t)1 << 30) || !sfc::any_loads_ok(lda, ldb, K, N)) return sfc::SmallChoice{0, 1, 0.0};
-  return sfc::small_choose(M, N, K, ob ? 2 : 4, st.num_cus, ca_layers, layers_ok);
+  return sfc::small_choose(M, N, K, ob ? 2 : 4, st.num_cus, ca_layers);
 }
 
 // The small-block kernel; its layer copies and counters lie in (W, counters), the
@@ -478,7 +477,7 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const
   // (a caller's workspace receives the layer copies of the plan: with the layer
   // count left to the library, that is the curve kernel's)
   if (tile == SFC_TILE_AUTO && !f8 && !(ws && ca_layers == SFC_CA_AUTO)) {
-    const sfc::SmallChoice sm = small_choice(*st, M, N, K, lda, ldb, ob, ca_layers, true);
+    const sfc::SmallChoice sm = small_choice(*st, M, N, K, lda, ldb, ob, ca_layers);
     if (sm.fm)
       return launch_small_plan(*st, sm.fm, sm.layers, M, N, K, A, lda, B, ldb, C, ldc, ob, stream);
   }
@@ -490,7 +489,7 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const
   // a partial last round
   Split sp;
   if (tile == SFC_TILE_AUTO) {
-    rc = plan_tail_split(*st, pl, M, N, K, A, lda, B, ldb, ob, f8, &sp);
+    rc = plan_tail_split(*st, pl, M, N, ob, f8, &sp);
     if (rc != SFC_OK) return rc;
   }
   const Fuse none;
@@ -592,7 +591,7 @@ int gemm_noalloc_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t ld
   float* W = reinterpret_cast<float*>(base);
 
   if (tile == SFC_TILE_AUTO) {
-    const sfc::SmallChoice sm = small_choice(*st, M, N, K, lda, ldb, ob, ca_layers, true);
+    const sfc::SmallChoice sm = small_choice(*st, M, N, K, lda, ldb, ob, ca_layers);
     const int64_t cells = sfc::ceil_div(M, 16 * (sm.fm ? sm.fm : 1)) * sfc::ceil_div(N, 64);
     if (sm.fm && sm.layers > 1) {
       if (cells > kNoAllocCells || (size_t)(cells * sm.layers) * (size_t)(16 * sm.fm * 64) * 4u > kNoAllocWsBytes)
@@ -611,7 +610,7 @@ int gemm_noalloc_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t ld
     return set_error(SFC_ERR_WORKSPACE, "sfc_gemm_noalloc_ex: the planned layer copies exceed its workspace");
   Split sp;
   if (tile == SFC_TILE_AUTO) {
-    rc = plan_tail_split(*st, pl, M, N, K, A, lda, B, ldb, ob, 0, &sp);
+    rc = plan_tail_split(*st, pl, M, N, ob, 0, &sp);
     if (rc != SFC_OK) return rc;
   }
   Plan main = pl;

@@ -1,18 +1,15 @@
 """When 256x256 blocks with a half-height strip take over from the model's 128x256
 blocks (host rule, compiled with g++ from paper_2601_16294_amd/csrc/sfc_model.cpp)."""
 import itertools
-import os
-import subprocess
 
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-HARNESS = r'''
-#include <stdio.h>
-#include "sfc_model.h"
-#include "sfc_params.h"
-#include "sfc_validate.h"
-int main() {
+import host_rule
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    return host_rule.build(str(tmp_path_factory.mktemp("strip")), r'''
   long long M, N, K; int ob;
   const int occ[4] = {2, 1, 1, 1};
   while (scanf("%lld %lld %lld %d", &M, &N, &K, &ob) == 4) {
@@ -20,26 +17,7 @@ int main() {
     const long long gm = (M + 255) / 256, gn = (N + 255) / 256;
     printf("%d %d %d\n", ch.tile == sfc::kT128x256, (int)sfc::strip_beats_128x256(M, N, (K + 63) / 64, ob, 256, ch),
            sfc::strip_columns((int)gm, (int)gn, 256, (M + 127) / 128, 256));
-  }
-  return 0;
-}
-'''
-
-
-@pytest.fixture(scope="module")
-def rule(tmp_path_factory):
-    d = tmp_path_factory.mktemp("strip")
-    src, exe = d / "h.cpp", d / "h"
-    src.write_text(HARNESS)
-    csrc = f"{ROOT}/paper_2601_16294_amd/csrc"
-    subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", f"-I{ROOT}/include",
-                    f"-I{csrc}", str(src), f"{csrc}/sfc_model.cpp", "-o", str(exe)], check=True)
-
-    def run(calls):
-        text = "\n".join(" ".join(str(v) for v in c) for c in calls)
-        out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
-        return [tuple(int(x) for x in line.split()) for line in out if line]
-    return run
+  }''')
 
 
 def test_measured_shapes(rule):
