@@ -118,3 +118,21 @@ def test_few_rows_in_the_last_blocks(M, tile):
     sg().sfc_gemm_fused_ex(upload(A), upload(B), C, ca_layers=3, tile=tile)
     want = obf16.bf16_to_f64(A) @ obf16.bf16_to_f64(B)
     assert np.array_equal(to_host(C), want)
+
+
+# element loads (rows of fewer than 8 elements, leading dimensions past the ring's 32-bit
+# offsets): several K blocks, a ragged last one, layers, every block shape
+@pytest.mark.parametrize("tile", TILES)
+@pytest.mark.parametrize("c", [1, 3])
+def test_element_loads(tile, c):
+    for M, N, K in ((300, 7, 520), (129, 3, 321), (270, 300, 7)):
+        check(M, N, K, tile, c, "f32", K + 1, N, N + 1, 2950 + N)
+        check(M, N, K, tile, c, "bf16", K, N + 2, N, 2960 + N)
+    M, N, K = 140, 264, 457
+    A, B = draw(M, K, ("int", -4, 4), 2970), draw(K, N, ("int", -4, 4), 2971)
+    big = torch.full((M, 1 << 20), float("nan"), dtype=torch.bfloat16, device="cuda")
+    big[:, :K] = upload(A)
+    C = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    sg().sfc_gemm_ex(big[:, :K], upload(B), C, ca_layers=c, tile=tile)
+    want = obf16.bf16_to_f64(A) @ obf16.bf16_to_f64(B)
+    assert np.array_equal(to_host(C), want)

@@ -100,8 +100,10 @@ def test_fused_equals_separate_and_counters_reset():
         ocheck.assert_gemm_close(to_host(Cf), Cr, R, f"fused {M}x{N}x{K} c={c} {tile}")
 
 
-def test_fused_one_layer_and_auto():
-    M, N, K = 256, 192, 8192
+# (the first shape runs on the small-block kernel either way, with no layer copies of
+# its own to fuse; the others on the curve kernel: c = 0 with layers and with one)
+@pytest.mark.parametrize("M,N,K", [(256, 192, 8192), (520, 512, 16384), (1100, 1100, 1000)])
+def test_fused_one_layer_and_auto(M, N, K):
     A = draw(M, K, ("normal", 0.0, 1.0), 9501)
     B = draw(K, N, ("normal", 0.0, 1.0), 9502)
     dA, dB = upload(A), upload(B)

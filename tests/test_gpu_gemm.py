@@ -65,7 +65,8 @@ def test_k_depths_and_tails_fast_path(K, tile):
 
 @pytest.mark.parametrize("tile", TILES)
 def test_vector_and_element_loads_agree_bitwise(tile):
-    # lda, ldb multiples of 8 take 128-bit loads; odd ones take element loads.
+    # lda, ldb multiples of 8 take 16-byte aligned loads, odd ones the same ring at any
+    # alignment, an lda of 2^20 or more element loads: the same products in the same order.
     M, N, K = 300, 264, 520
     A8, B8 = operands(M, N, K, 300, lda=528, ldb=272)
     A7 = np.ascontiguousarray(np.pad(A8[:, :K], ((0, 0), (0, 3)), constant_values=0x7FC0))
@@ -73,6 +74,9 @@ def test_vector_and_element_loads_agree_bitwise(tile):
     c8 = run_gemm(A8, B8, M, N, K, tile=tile)
     c7 = run_gemm(A7, B7, M, N, K, tile=tile)
     assert np.array_equal(c8, c7)
+    wide = torch.full((M, 1 << 20), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wide[:, :K] = upload(A8)[:, :K]
+    assert np.array_equal(c8, run_gemm(None, B8, M, N, K, tile=tile, dev_A=wide))
     Cr, R = oracle(A8, B8, M, N, K)
     ocheck.assert_gemm_close(c8[:, :N], Cr, R)
 
@@ -214,10 +218,12 @@ def test_mfma_probe_runs():
         assert 100.0 < v["tflops"] < 3000.0 and 500.0 < v["mhz"] < 3000.0
 
 
-@pytest.mark.parametrize("M,N,K,out", [(256, 192, 8192, "f32"), (300, 520, 4104, "bf16"), (64, 64, 20000, "f32")])
+@pytest.mark.parametrize("M,N,K,out", [(256, 192, 8192, "f32"), (300, 520, 4104, "bf16"), (64, 64, 20000, "f32"),
+                                       (520, 512, 16384, "f32"), (700, 2000, 4200, "bf16")])
 def test_auto_layers_match_oracle(M, N, K, out):
-    """SFC_CA_AUTO: the model's block shape and layer count (row f1), checked
-    against the fp64 oracle; on these K-dominant shapes it picks layers."""
+    """SFC_CA_AUTO on K-dominant shapes, checked against the fp64 oracle: the
+    library's choice (the small-block kernel for the first three), and with a
+    workspace the model's block shape and layer count, whose copies are left there."""
     A, B = operands(M, N, K, 700 + M)
     C = run_gemm(A, B, M, N, K, out=out, ca_layers=0)
     Cr, R = oracle(A, B, M, N, K)
@@ -230,6 +236,14 @@ def test_auto_layers_match_oracle(M, N, K, out):
     model = sg().sfc_gemm_model(M, N, K, out="f32", ca_layers=0, num_cus=cus, occupancy=occ)
     assert (f"{plan['BM']}x{plan['BN']}", plan["layers"]) == (model["tile"], model["layers"])
     assert plan["layers"] > 1
+    ws = torch.full((sg().sfc_gemm_ws_size(M, N, K, 0) // 4,), float("nan"), dtype=torch.float32, device="cuda")
+    C = run_gemm(A, B, M, N, K, out=out, ca_layers=0, workspace=ws)
+    ocheck.assert_gemm_close(C, Cr, R, f"auto {M}x{N}x{K} {out} with a workspace")
+    W = ws.cpu().numpy().reshape(-1, M, N)
+    assert np.isnan(W[plan["layers"]:]).all()
+    red = oca.reduce_layers_f32(W[:plan["layers"]])
+    want = obf16.bf16_to_f64(obf16.f32_to_bf16_rne(red)) if out == "bf16" else red.astype(np.float64)
+    assert np.array_equal(C, want)
 
 
 @pytest.mark.parametrize("tile", TILES)

@@ -96,14 +96,15 @@ def test_two_streams_at_once():
 
 
 def test_two_streams_with_layers():
-    """sfc_gemm with c = 2 and with SFC_CA_AUTO (layers chosen by the model,
-    more than one on these K-dominant shapes), using the library's own
+    """sfc_gemm with c = 2 and with SFC_CA_AUTO (layers chosen by the library,
+    more than one on these K-dominant shapes: on the small-block kernel first,
+    on the curve kernel in each stream's last call), using the library's own
     workspace, enqueued on two default-priority streams before either is waited
-    for; each stream also grows its workspace between its two calls.  Every
-    result meets the bar against the oracle."""
+    for; each stream also grows its workspace between its calls.  Every result
+    meets the bar against the oracle."""
     plan = [  # per stream: (M, N, K, ca_layers, seed), in enqueue order
-        [(256, 192, 8192, 2, 7401), (320, 256, 16384, 0, 7411)],
-        [(300, 200, 12288, 0, 7421), (512, 384, 6144, 2, 7431)],
+        [(256, 192, 8192, 2, 7401), (320, 256, 16384, 0, 7411), (520, 512, 16384, 0, 7441)],
+        [(300, 200, 12288, 0, 7421), (512, 384, 6144, 2, 7431), (520, 1100, 6144, 0, 7451)],
     ]
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]
     jobs = []

@@ -5,8 +5,6 @@ import pytest
 import host_api
 from host_api import gemm
 
-LOAD_ELEMENTS = 0
-
 
 @pytest.fixture(scope="module")
 def exe(tmp_path_factory):
@@ -130,3 +128,27 @@ def test_fp8_shape_without_a_strip(exe):
                 M, N = 4096, 256 * (16 * R + w)
                 g = [e["tile"] for _, e in launches(host_api.run(exe, [gemm("f8", M, N, K, 1)])[0])]
                 assert len(g) == 1
+
+
+# the loads that the tests of each path mean to reach, and which calls of theirs run on
+# the small-block kernel
+def test_load_paths(exe):
+    def one(*a, **k):
+        return launches(host_api.run(exe, [gemm("ex", *a, **k)])[0])[0]
+    ELEMENTS, RING, ANY = 0, 1, 2
+    for tile in (1, 2, 3, 4):
+        assert one(300, 264, 520, tile=tile, lda=528, ldb=272)[1]["loads"] == RING
+        assert one(300, 264, 520, tile=tile, lda=531, ldb=277)[1]["loads"] == ANY
+        assert one(300, 264, 520, tile=tile, lda=1 << 20)[1]["loads"] == ELEMENTS
+        assert one(300, 264, 520, tile=tile, ldb=1 << 22)[1]["loads"] == ELEMENTS
+        for c in (1, 3):
+            assert one(300, 7, 520, ca=c, tile=tile)[1]["loads"] == ELEMENTS
+            assert one(270, 300, 7, ca=c, tile=tile)[1]["loads"] == ELEMENTS
+    for entry in ("ex", "fused"):
+        for M, N, K, ca, kernel in ((256, 192, 8192, 0, "small"), (256, 192, 8192, 1, "small"), (300, 200, 12288, 0, "small"),
+                                    (520, 512, 16384, 0, "gemm"), (520, 1100, 6144, 0, "gemm"), (700, 2000, 4200, 0, "gemm"),
+                                    (1100, 1100, 1000, 0, "gemm"), (1100, 1100, 1000, 1, "gemm")):
+            name, e = launches(host_api.run(exe, [gemm(entry, M, N, K, ca=ca)])[0])[0]
+            assert name == kernel and (ca == 1 or (M, N) == (1100, 1100) or e["layers"] > 1), (M, N, K, ca)
+        # a caller's workspace gets the model's copies
+        assert launches(host_api.run(exe, [gemm(entry, 256, 192, 8192, ca=0, ws=1)])[0])[0][0] == "gemm"
