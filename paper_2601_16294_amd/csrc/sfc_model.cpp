@@ -104,6 +104,14 @@ bool strip_beats_128x256(int64_t M, int64_t N, int64_t nk, int out_bytes, int nu
 // (128-byte row segments of B; the curve kernel's 512-byte ones reach 6.0); with
 // several layers 2.2 us for the count's round trip and the last workgroup's read
 // of a block's copies at about 30 bytes per ns.
+// Past 150 MB the small-block kernel slows down where a workgroup has many rounds
+// (curve kernel in 4 or 8 layers -> small, us: 16x12520x7656 40.0 -> 44.9, 15x14200x8200
+// 44.6 -> 48.2, 56x14848x9288 61.9 -> 73.6; below 26 rounds the small one wins: 3x16208x5728
+// 35.7 -> 31.5, 15x14624x6224 37.6 -> 34.2; against 16 layers, whose tasks fill the
+// curve kernel's rounds badly, up to 40: 3x12256x8552 50.5 -> 39.1, 13x11768x12040 64.2 ->
+// 66.0), unless one 16-row block reads whole 128-byte lines (16x13376x6840 37.3 -> 32.8,
+// 12x11840x12352 64.5 -> 49.2), and where rows of B lie a multiple of 4 KB apart, which puts a block's segments
+// on few channels (16x16384x6144 40.3 -> 41.7, 16x16384x8192 50.9 -> 54.5).
 SmallChoice small_choose(int64_t M, int64_t N, int64_t K, int out_bytes, int num_cus, int ca_layers) {
   SmallChoice best{0, 1, 1e300};
   // more blocks than CUs of the tallest shape (a second round of workgroups would
@@ -116,7 +124,11 @@ SmallChoice small_choose(int64_t M, int64_t N, int64_t K, int out_bytes, int num
   double old_us = old.clk / 2100.0;
   const double old_mem = 4.0 + in_bytes / 6.0e6 + (old.layers > 1 ? 4.0 + old.layers * mn * 8.0 / 4.0e6 : 0.0);
   if (old_mem > old_us) old_us = old_mem;
-  static const double kLow[3] = {0.42, 0.50, 0.62}, kHigh[3] = {0.60, 0.66, 0.86}, kCold[3] = {0.90, 0.95, 1.05};
+  static const double kLow[3] = {0.42, 0.50, 0.62}, kHigh[3] = {0.60, 0.66, 0.86}, kCold[3] = {0.90, 0.95, 1.05},
+                      kLong[3] = {1.40, 1.48, 1.56};
+  const bool large = in_bytes > 150e6;
+  const bool whole_lines = N % 64 == 0 && N % 1024 != 0;
+  const double stream = large && old.layers <= 4 && N % 2048 == 0 ? 4.9e6 : 5.2e6;
   const int64_t nk = cdiv(K, 64);
   for (int i = 0; i < 3; ++i) {
     const int fm = 1 << i;
@@ -128,10 +140,11 @@ SmallChoice small_choose(int64_t M, int64_t N, int64_t K, int out_bytes, int num
       const double rounds = (double)cdiv(nk, 4 * c);
       const double busy = (double)(tiles * c) / (double)num_cus;
       double per = kLow[i] + (kHigh[i] - kLow[i]) * busy;
-      const double arrive = in_bytes > 60e6 ? 1.3 * kCold[i] : in_bytes > 16e6 ? kCold[i] : 0.0;
+      const bool many = large && rounds > (old.layers > 8 ? 40.0 : 25.0) && !(i == 0 && whole_lines);
+      const double arrive = many ? kLong[i] : in_bytes > 60e6 ? 1.3 * kCold[i] : in_bytes > 16e6 ? kCold[i] : 0.0;
       if (per < arrive) per = arrive;
       double us = rounds * per;
-      if (us < in_bytes / 5.2e6) us = in_bytes / 5.2e6;
+      if (us < in_bytes / stream) us = in_bytes / stream;
       us += 3.0 + mn * out_bytes / 4.0e6;
       if (c > 1) us += 2.2 + (double)(fm * c) * 4096.0 / 30.0e3;
       if (us < best.us) best = SmallChoice{fm, c, us};

@@ -27,8 +27,27 @@ def test_choices(choose):
         (32, 14336, 4096, 2, 0): (2, 1),
         (1024, 1024, 1024, 2, 1): (4, 1),
         (128, 128, 65535, 4, 0): (1, 16),
+        # large weights: many rounds of K, or rows of B that meet on few channels, leave
+        # them to the curve kernel; timed on both sides
+        (16, 12520, 7656, 2, 0): (0, 1),
+        (1, 12520, 7656, 2, 0): (0, 1),
+        (16, 16384, 8192, 2, 0): (0, 1),
+        (4, 16384, 6144, 2, 0): (0, 1),
+        (16, 12288, 12288, 2, 0): (0, 1),
+        (12, 11840, 12352, 2, 0): (1, 1),
+        (16, 13376, 6840, 2, 0): (1, 1),
+        (16, 13640, 6808, 2, 0): (0, 1),
+        (58, 13056, 7680, 2, 0): (0, 1),
+        (16, 12288, 8192, 2, 0): (1, 1),
+        (33, 16384, 6144, 2, 0): (4, 1),
+        (1, 16336, 4712, 2, 0): (1, 1),
+        (16, 8192, 8192, 2, 0): (1, 2),
+        (3, 3096, 12560, 2, 0): (1, 4),
+        (20, 6688, 9280, 2, 0): (2, 2),
+        (209, 1464, 9296, 4, 0): (0, 1),
     }
-    assert choose(calls.keys()) == list(calls.values())
+    got = [(fm, layers if fm else 1) for fm, layers in choose(calls.keys())]
+    assert got == list(calls.values())
     for c in [(1024, 2048, 512, 2, 1), (8192, 8192, 8192, 2, 0), (16, 16384, 16384, 2, 0), (64, 64, 7, 4, 1)]:
         assert choose([c])[0][0] == 0, c
 
