@@ -55,11 +55,17 @@ extern "C" {
                                     launch (same stream) with 128-row blocks of the
                                     same width, which fill one round in about half
                                     the time; result bits are those of the single
-                                    launch.  Small products and few rows with
-                                    ca_layers SFC_CA_AUTO or 1 run on a kernel of
-                                    16-, 32- or 64-row blocks (not with a caller's
-                                    workspace and SFC_CA_AUTO: its layer copies
-                                    are those of sfc_gemm_plan) */
+                                    launch.  (fp8 operands: only where K is deep
+                                    enough for that to pay.)  256x256 blocks with
+                                    such a launch may also take the place of the
+                                    128x256 blocks that sfc_gemm_model prefers.
+                                    Small bf16 products and few rows with ca_layers
+                                    SFC_CA_AUTO or 1 run on a kernel of 16-, 32- or
+                                    64-row blocks, which are all in flight at once:
+                                    order and sched are checked but mean nothing
+                                    there (not with a caller's workspace and
+                                    SFC_CA_AUTO: its layer copies are those of
+                                    sfc_gemm_plan) */
 #define SFC_TILE_128x128 1
 #define SFC_TILE_256x128 2       /* BM = 256, BN = 128 */
 #define SFC_TILE_128x256 3       /* BM = 128, BN = 256 */
@@ -68,7 +74,9 @@ extern "C" {
 /* ---- number of K layers (copies of C) ---------------------------------- */
 #define SFC_CA_AUTO      0       /* ca_layers = 0: chosen with the block shape by the
                                     analytical model (Section III.B Eq. 1-4, used as in
-                                    Section III.C's second option), among 1, 2, 4, 8, 16 */
+                                    Section III.C's second option), among 1, 2, 4, 8, 16;
+                                    small products and few rows on their own kernel take
+                                    a count of their own, among the same */
 
 /* ---- order of the output blocks ---------------------------------------- */
 #define SFC_ORDER_HILBERT   0    /* generalized Hilbert curve (Section II.B) */
@@ -121,7 +129,9 @@ int sfc_tile_order_ex(int gm, int gn, int order, int32_t *out_idx);
  *              is never freed, so replays may run on any stream and beside calls
  *              that run at once.  Replays of graphs that were recorded on one
  *              stream must not overlap each other.
- *              SFC_CA_AUTO (0): the model picks c (see sfc_gemm_model).
+ *              SFC_CA_AUTO (0): the library picks c (sfc_gemm_model's, or the
+ *              small-block kernel's own: 13x1024x16384 takes 8 there, the model
+ *              16).
  *   stream     hipStream_t or NULL.
  * No GEMM entry point synchronises the device or a stream.  The first call for
  * a block grid allocates its curve table (hipMalloc) and enqueues the
@@ -233,8 +243,9 @@ int sfc_gemm_noalloc_ex(int64_t M, int64_t N, int64_t K,
  * free knobs with the model of sfc_gemm_model over those two block shapes,
  * evaluated on the bf16 problem with the same number of K blocks (K' =
  * 64*ceil(K/128)): a 128-deep fp8 block moves the bytes of a 64-deep bf16
- * block and takes the same MFMA time (ties go to 256x256).  Other arguments and
- * errors as for sfc_gemm_ex.
+ * block and takes the same MFMA time (ties go to 256x256); a half-height last
+ * launch may then change 128x256 to 256x256 blocks (see SFC_TILE_AUTO).  K = 0
+ * writes zeros for any N.  Other arguments and errors as for sfc_gemm_ex.
  */
 int sfc_gemm_f8_ex(int64_t M, int64_t N, int64_t K,
                    const void *A, int64_t lda,
@@ -267,9 +278,10 @@ int sfc_gemm_f8_fmt_ex(int64_t M, int64_t N, int64_t K,
 /*
  * sfc_gemm_plan -- what sfc_gemm_ex would launch, without launching
  * (fp32 output, 16-byte aligned operands).  ca_layers may be SFC_CA_AUTO and
- * tile SFC_TILE_AUTO; the plan then shows the model's choice (for the whole
- * grid: a half-height strip that SFC_TILE_AUTO may add is not shown, nor the
- * small-block kernel that SFC_TILE_AUTO uses for small products and few rows).
+ * tile SFC_TILE_AUTO; the plan then shows the choice of the curve kernel, for the
+ * whole grid: the model's, or the 256x256 blocks that replace it together with a
+ * half-height strip.  The strip itself is not shown, nor the small-block kernel
+ * that SFC_TILE_AUTO uses for small products and few rows.
  *   plan[0] = BM, plan[1] = BN, plan[2] = gm, plan[3] = gn, plan[4] = c_eff,
  *   plan[5] = number of persistent workgroups, plan[6] = workgroups per CU.
  * Needs a device (it queries the CU count and kernel occupancy).
@@ -286,7 +298,10 @@ int sfc_gemm_f8_plan(int64_t M, int64_t N, int64_t K, int ca_layers, int tile, i
 
 /*
  * sfc_gemm_model -- the analytical model behind SFC_TILE_AUTO and SFC_CA_AUTO,
- * evaluated for given device parameters (host only: no device is touched).
+ * evaluated for given device parameters (host only: no device is touched).  Two
+ * measured rules come after it: small products and few rows may run on the
+ * small-block kernel, and 256x256 blocks with a half-height strip may replace
+ * 128x256 blocks (see SFC_TILE_AUTO); both are outside this function.
  * The paper's fine-grained roofline (Section III.B, Eq. 1-4) on the GPU: a core
  * is a CU running `occupancy` persistent workgroups, one BRGEMM is one 64-deep
  * block of one task, at max(G*gamma, beta*(S_A + S_B)) with the panels of a

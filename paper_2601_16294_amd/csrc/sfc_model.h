@@ -66,8 +66,9 @@ struct SmallChoice {
   double us;
 };
 
-// ca_layers 0 (free) or 1.  Measured on MI355X, cold operands, against the curve kernel (us):
-//   512x512x512 f32 8.2 -> 4.2, 333x517x421 bf16 10.8 -> 4.7, 1024^3 bf16 11.6 -> 8.4,
+// ca_layers 0 (free) or 1.  Measured on MI355X, calls of the C ABI back to back over
+// rotating operands, against the curve kernel (us):
+//   512x512x512 f32 8.2 -> 4.6, 333x517x421 bf16 10.8 -> 4.9, 1024^3 bf16 11.6 -> 8.4,
 //   16x14336x4096 bf16 28.3 -> 25.7, 1x4096x4096 16.4 -> 10.0, 64x14336x4096 36.7 -> 30.8,
 //   256x4096x4096 20.2 -> 17.2, 200x200x5999 f32 (one layer) 64.3 -> 19.0;
 // and where the curve kernel stays: 16x16384x16384 92 (small 106), 512x512x32768 34

@@ -23,7 +23,8 @@
 // 28.1 -> 25.7 us; the curve kernel's 128-row blocks needed 4 layer copies and a
 // reduction launch for the same parallelism).  Small products are a chain of
 // launch (~2 us), first loads (~1 us), rounds of 256 of K (0.4-0.9 us) and the sum of
-// the partial blocks: 512x512x512 f32 8.2 -> 4.2 us, 333x517x421 bf16 10.8 -> 4.7.
+// the partial blocks.  Calls of the C ABI back to back: 512x512x512 f32 8.2 -> 4.6 us,
+// 333x517x421 bf16 10.8 -> 4.9 (5.1 both in a kernel trace, which spaces the launches).
 //
 // Rows of any alignment (see the notes at any_tail in sfc_gemm_kernel.h): the ring
 // takes whole stages; where K is no multiple of 32, or a last chunk of a row of B
