@@ -128,3 +128,40 @@ def test_fused_integer_inputs_exact():
         sg().sfc_gemm_fused_ex(upload(A), upload(B), C, ca_layers=c, tile=tile)
         torch.cuda.synchronize()
         assert np.array_equal(to_host(C), Cr), (c, tile)
+
+
+# calls with layer copies recorded into a graph (the separate and the fused reduction,
+# on a stream with and without library memory): each replay, beside eager calls that
+# grow the stream's memory and on another stream, gives the eager bits
+@pytest.mark.parametrize("warm", [False, True])
+@pytest.mark.parametrize("fn,c,tile", [("sfc_gemm_ex", 0, "auto"), ("sfc_gemm_ex", 3, "128x128"),
+                                       ("sfc_gemm_fused_ex", 0, "auto"), ("sfc_gemm_fused_ex", 4, "128x256")])
+def test_recorded_layers_keep_the_bits(fn, c, tile, warm):
+    M, N, K = 520, 512, 16384
+    f = getattr(sg(), fn)
+    dA, dB = upload(draw(M, K, ("normal", 0.0, 1.0), 9701)), upload(draw(K, N, ("normal", 0.0, 1.0), 9702))
+    lA, lB = upload(draw(1100, 4096, ("normal", 0.0, 1.0), 9703)), upload(draw(4096, 1200, ("normal", 0.0, 1.0), 9704))
+    want, got, eager = (torch.empty((M, N), device="cuda") for _ in range(3))
+    large = torch.empty((1100, 1200), device="cuda")
+    for _ in range(2):                        # the curve tables are known to be complete
+        f(dA, dB, want, ca_layers=c, tile=tile)
+        f(lA, lB, large, ca_layers=8, tile="256x256")
+        torch.cuda.synchronize()
+    s, t = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        if warm:
+            f(dA, dB, eager, ca_layers=c, tile=tile)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            f(dA, dB, got, ca_layers=c, tile=tile)
+        for replay_on in (s, t, s):
+            got.fill_(float("nan"))
+            f(lA, lB, large, ca_layers=8, tile="256x256")
+            f(dA, dB, eager, ca_layers=c, tile=tile)
+            torch.cuda.synchronize()
+            with torch.cuda.stream(replay_on):
+                g.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(raw_bits(got), raw_bits(want))
+            assert np.array_equal(raw_bits(eager), raw_bits(want))
