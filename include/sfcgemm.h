@@ -135,7 +135,9 @@ int sfc_tile_order_ex(int gm, int gn, int order, int32_t *out_idx);
  *   stream     hipStream_t or NULL.
  * No GEMM entry point synchronises the device or a stream.  The first call for
  * a block grid allocates its curve table (hipMalloc) and enqueues the
- * generator on `stream`; calls on other streams wait for it on the device.
+ * generator on `stream`; calls on other streams wait for it on the device.  A
+ * call recorded into a graph before the table is complete has the generator in
+ * the graph.
  */
 int sfc_gemm(int64_t M, int64_t N, int64_t K,
              const void *A, int64_t lda,

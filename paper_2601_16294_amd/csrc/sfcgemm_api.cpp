@@ -54,6 +54,7 @@ struct StreamMem {
 
 struct DeviceState {
   std::map<std::tuple<int, int, int>, Table> tables;   // (gm, gn, order) -> device table
+  std::map<std::tuple<int, int, int>, int32_t*> captured_tables;   // those that graphs write themselves
   std::map<hipStream_t, StreamMem> streams;
   char* scratch = nullptr;   // this device's copy of `scratch` (see sfc_gemm_noalloc_ex)
   int num_cus = 0;
@@ -89,28 +90,81 @@ int device_state(DeviceState** out) {
   return SFC_OK;
 }
 
+// Whether calls on `stream` are being recorded into a graph.
+bool is_captured(hipStream_t stream) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
+    (void)hipGetLastError();   // not an error: do not leave it for the next check
+    return false;
+  }
+  return cap != hipStreamCaptureStatusNone;
+}
+
+// The relaxed capture mode of this thread: allocations and event queries are refused
+// while a stream is captured in the other modes.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  hipError_t e;
+  RelaxedCapture() { e = hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() {
+    if (e == hipSuccess) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+};
+
+// Memory for a captured call: a plain allocation (one in stream order would become a
+// node of the graph and its memory the graph's).
+hipError_t captured_malloc(void** out, size_t bytes) {
+  RelaxedCapture relaxed;
+  return relaxed.e != hipSuccess ? relaxed.e : hipMalloc(out, bytes);
+}
+
 // Curve table of a gm x gn grid on the current device.  The first call for a
 // grid allocates it and enqueues the generator on `stream` (no wait); a later
 // call on another stream waits for that kernel on the device, until the table
-// is known to be complete.  Must be called with g_mu held.
+// is known to be complete.  A call that is recorded into a graph before that cannot
+// wait for it: it records the generator too, into a table that only recorded calls
+// use (each replay writes the same values).  Must be called with g_mu held.
 int get_table(DeviceState& st, int gm, int gn, int order, hipStream_t stream, const int32_t** out) {
   auto key = std::make_tuple(gm, gn, order);
   auto it = st.tables.find(key);
-  if (it != st.tables.end()) {
+  const bool known = it != st.tables.end();
+  if (known && it->second.done) {
+    *out = it->second.d;
+    return SFC_OK;
+  }
+  const bool cap = is_captured(stream);
+  if (known) {
     Table& t = it->second;
-    if (!t.done) {
-      hipError_t e = hipEventQuery(t.ready);
-      if (e == hipSuccess) {
-        t.done = true;
-      } else if (e == hipErrorNotReady) {
-        (void)hipGetLastError();   // not an error: do not leave it for the next check
-        e = hipStreamWaitEvent(stream, t.ready, 0);
-        if (e != hipSuccess) return hip_fail(e, "hipStreamWaitEvent(curve table)");
-      } else {
-        return hip_fail(e, "hipEventQuery(curve table)");
-      }
+    hipError_t e;
+    {
+      RelaxedCapture relaxed;
+      e = hipEventQuery(t.ready);
     }
-    *out = t.d;
+    if (e == hipSuccess) {
+      t.done = true;
+    } else if (e == hipErrorNotReady) {
+      (void)hipGetLastError();   // not an error: do not leave it for the next check
+      if (!cap) e = hipStreamWaitEvent(stream, t.ready, 0);
+      if (!cap && e != hipSuccess) return hip_fail(e, "hipStreamWaitEvent(curve table)");
+    } else {
+      return hip_fail(e, "hipEventQuery(curve table)");
+    }
+    if (t.done || !cap) {
+      *out = t.d;
+      return SFC_OK;
+    }
+  }
+  if (cap) {
+    int32_t*& d = st.captured_tables[key];
+    if (!d) {
+      void* p = nullptr;
+      hipError_t e = captured_malloc(&p, sizeof(int32_t) * (size_t)gm * (size_t)gn);
+      if (e != hipSuccess) return hip_fail(e, "hipMalloc(curve table of captured calls)");
+      d = static_cast<int32_t*>(p);
+    }
+    hipError_t e = sfc::launch_sfc_order(gm, gn, order, d, stream);
+    if (e != hipSuccess) return hip_fail(e, "curve table");
+    *out = d;
     return SFC_OK;
   }
   Table t;
@@ -126,28 +180,6 @@ int get_table(DeviceState& st, int gm, int gn, int order, hipStream_t stream, co
   st.tables[key] = t;
   *out = t.d;
   return SFC_OK;
-}
-
-// Whether calls on `stream` are being recorded into a graph.
-bool is_captured(hipStream_t stream) {
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
-    (void)hipGetLastError();   // not an error: do not leave it for the next check
-    return false;
-  }
-  return cap != hipStreamCaptureStatusNone;
-}
-
-// Memory for a captured call: a plain allocation, which is refused during a capture
-// unless the thread is in the relaxed mode (an allocation in stream order would
-// become a node of the graph and its memory the graph's).
-hipError_t captured_malloc(void** out, size_t bytes) {
-  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-  hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
-  if (e != hipSuccess) return e;
-  e = hipMalloc(out, bytes);
-  const hipError_t back = hipThreadExchangeStreamCaptureMode(&mode);
-  return e != hipSuccess ? e : back;
 }
 
 // At least `bytes` of layer workspace owned by `stream`.  Outside a capture a

@@ -7,6 +7,7 @@ allocation and launch: what a call would do on the device, checked without one.
   gemm <entry> M N K lda ldb ldc out ca tile ws stream    entry: ex, fused, noalloc, f8
   capture <stream> <0|1>                                  a capture begins or ends
   fail <n>                                                the n-th allocation from here fails
+  notready <0|1>                                          events report unfinished work
 Every command ends with a ``ret`` event that holds the return code.  Addresses are
 numbers counted up from 2^40; ``ws`` is 1 for a caller's workspace, else 0."""
 import os
@@ -23,7 +24,7 @@ HIP = r'''
 #define __align__(n) __attribute__((aligned(n)))
 #define HIP_SYMBOL(x) (&x)
 enum hipError_t { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorOutOfMemory = 2, hipErrorNotReady = 600,
-                  hipErrorStreamCaptureUnsupported = 900, hipErrorStreamCaptureImplicit = 906 };
+                  hipErrorStreamCaptureUnsupported = 900, hipErrorStreamCaptureIsolation = 905, hipErrorStreamCaptureImplicit = 906 };
 typedef struct ihipStream_t* hipStream_t;
 typedef struct ihipEvent_t* hipEvent_t;
 enum { hipEventDisableTiming = 2, hipDeviceAttributeMultiprocessorCount = 1, hipMemcpyDeviceToHost = 2 };
@@ -63,7 +64,7 @@ MAIN = r'''
 static uintptr_t next_addr = (uintptr_t)1 << 40;
 static std::set<hipStream_t> capturing;
 static hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
-static int fail_in = 0;
+static int fail_in = 0, not_ready = 0;
 static hipError_t take(const char* what, void** p, size_t n, hipStream_t s) {
   if (fail_in && --fail_in == 0) return hipErrorOutOfMemory;
   *p = (void*)next_addr;
@@ -85,10 +86,15 @@ const char* hipGetErrorString(hipError_t) { return "error"; }
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, int, int) { *v = 256; return hipSuccess; }
-hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) {
+  if (!capturing.empty() && mode != hipStreamCaptureModeRelaxed) return hipErrorStreamCaptureUnsupported;
+  return not_ready ? hipErrorNotReady : hipSuccess;
+}
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t)8; return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
-hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t, unsigned) {
+  return capturing.count(s) ? hipErrorStreamCaptureIsolation : hipSuccess;   // an event from outside the capture
+}
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
   *st = capturing.count(s) ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
   return !s && !capturing.empty() ? hipErrorStreamCaptureImplicit : hipSuccess;
@@ -113,8 +119,8 @@ hipError_t launch_sfc_order(int gm, int gn, int order, int32_t* d, hipStream_t) 
   return hipSuccess;
 }
 hipError_t launch_gemm(const Variant& v, const GemmParams& p, int grid, hipStream_t) {
-  printf("gemm tile=%d bf16=%d loads=%d f8=%d deep=%d M=%ld N=%ld K=%ld layers=%d out=%lu counters=%lu grid=%d\n", v.tile,
-         (int)v.out_bf16, v.loads, v.f8, (int)v.deep, (long)p.M, (long)p.N, (long)p.K, p.layers, u(p.out), u(p.counters), grid);
+  printf("gemm tile=%d bf16=%d loads=%d f8=%d deep=%d M=%ld N=%ld K=%ld layers=%d out=%lu counters=%lu grid=%d table=%lu\n", v.tile,
+         (int)v.out_bf16, v.loads, v.f8, (int)v.deep, (long)p.M, (long)p.N, (long)p.K, p.layers, u(p.out), u(p.counters), grid, u(p.table));
   return hipSuccess;
 }
 hipError_t gemm_occupancy(const Variant& v, int* n) { *n = v.tile == kT128x128 && !v.deep ? 2 : 1; return hipSuccess; }
@@ -157,6 +163,8 @@ int main() {
       if (on) capturing.insert((hipStream_t)stream);
       else capturing.erase((hipStream_t)stream);
       if (mode != hipStreamCaptureModeGlobal) return 2;      // left as the library found it
+    } else if (!strcmp(cmd, "notready")) {
+      if (scanf("%d", &not_ready) != 1) return 1;
     } else if (!strcmp(cmd, "fail")) {
       if (scanf("%d", &fail_in) != 1) return 1;
     } else {

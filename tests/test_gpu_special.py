@@ -127,3 +127,30 @@ def test_two_streams_with_layers():
             assert sg().sfc_gemm_plan(Mx, Nx, Kx, 0, "auto")["layers"] > 1
         Cr, R = ogemm.gemm_ref_rows(A, B, Nx, Kx, Kx, Nx, M=Mx)
         ocheck.assert_gemm_close(to_host(C), Cr, R, f"stream GEMM {Mx}x{Nx}x{Kx} c={c}")
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(1931, 2745, 520, "128x128"), (4873, 9011, 136, "auto"), (16, 12520, 7656, "auto")])
+def test_recorded_before_its_curve_table_exists(M, N, K, tile):
+    """The first call of a block grid may be recorded into a graph: every replay,
+    with eager calls of the same grid between them, writes the eager result.
+    Integer operands make every sum exact."""
+    A, B = draw(M, K, ("int", -2, 2), 7501), draw(K, N, ("int", -2, 2), 7502)
+    dA, dB = upload(A), upload(B)
+    C = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    E = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    c = 0 if M == 16 else 1
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        sg().sfc_gemm_ex(dA, dB, C, ca_layers=c, tile=tile, stream=s)
+    rows = [0, M // 2, M - 1]
+    want = obf16.bf16_to_f64(A[rows]) @ obf16.bf16_to_f64(B)
+    for _ in range(3):
+        C.fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        sg().sfc_gemm_ex(dA, dB, E, ca_layers=c, tile=tile)
+        torch.cuda.synchronize()
+        assert torch.equal(C, E)
+        assert np.array_equal(to_host(C[rows]), want)

@@ -152,3 +152,28 @@ def test_load_paths(exe):
             assert name == kernel and (ca == 1 or (M, N) == (1100, 1100) or e["layers"] > 1), (M, N, K, ca)
         # a caller's workspace gets the model's copies
         assert launches(host_api.run(exe, [gemm(entry, 256, 192, 8192, ca=0, ws=1)])[0])[0][0] == "gemm"
+
+
+# a recorded call whose block grid has no finished curve table yet (the first call of a
+# grid, or one whose generator may still run) records the generator and writes a table
+# that only recorded calls use; a finished table is used as it is
+@pytest.mark.parametrize("call", [gemm("ex", 900, 1300, 600, tile=3), gemm("ex", 4000, 14000, 1000), gemm("ex", 16, 12520, 7656, ca=0)])
+def test_recorded_calls_without_a_curve_table(exe, call):
+    lines = ["capture 1 1", call, call, "capture 1 0", call, "notready 1", "capture 1 1", call, "capture 1 0", "notready 0",
+             "capture 1 1", call, call, "capture 1 0", call]
+    calls = host_api.run(exe, lines)
+    assert all(c[-1] == ("ret", {"rc": 0}) for c in calls)
+    cold, again, eager, pending, done, done2, last = (calls[i] for i in (1, 2, 4, 7, 11, 12, 14))
+
+    def tables(events):
+        return [e["table"] for n, e in events if n == "gemm"]
+
+    def orders(events):
+        return [e["d"] for n, e in events if n == "order"]
+    for c in (cold, again, pending):
+        assert orders(c) == tables(c) and len(set(tables(c))) == len(tables(c))
+        assert tables(c) == tables(cold)
+    assert not set(tables(eager)) & set(tables(cold)) and orders(eager) == tables(eager)
+    for c in (done, done2, last):
+        assert tables(c) == tables(eager) and not orders(c)
+    assert not [e for n, e in again + pending + done if n == "malloc"]
