@@ -115,10 +115,11 @@ inline int strip_columns(int gm, int gn, int64_t slots, int64_t half_rows, int64
 // round of `left` blocks after `full` whole rounds.  An fp8 block takes half the time of
 // a bf16 one, and a part-filled round runs at a higher clock, so the strip's launch
 // (3-6 us) weighs more.  Timed against one launch of 256x256 blocks, 4096 rows, bf16 out,
-// several boxes (time of the one launch over that with the strip):
+// several cards (time of the one launch over that with the strip):
 //   2 rounds + 1/8 .. 1/2: K 3072-4096 1.02-1.11 (K 2048-2560: the model's 128x256 blocks);
 //   3 rounds + 3/16 .. 7/16: K 2048-4096 1.01-1.05, 8192 1.06; K 256-1024 0.97-1.01;
-//   3 rounds + 1/2: K 4096-8192 1.00-1.03, 3072 0.99-1.00, 2048 0.99-1.04, 256-512 0.96-0.97;
+//   3 rounds + 1/2: K 4096-8192 0.99-1.04 (mean 1.01), 3072 0.99-1.00, 2048 0.99-1.04,
+//     256-512 0.96-0.97;
 //   3 rounds + 1/16, 1/8: K 8192 1.02, 4096 0.99-1.02, 2048 0.97-1.01, 256-1024 0.95-0.99;
 //   4 or 6 rounds + 1/8: K 2048 0.98-0.99, 256-1024 0.90-0.94; 5 + 1/4: K 8192 1.01.
 inline bool f8_strip_pays(int64_t nk, int64_t full, int64_t left, int64_t slots) {

@@ -105,7 +105,7 @@ def test_whole_blocks_only_with_their_strip(exe, M, N, K):
 
 
 # the strip of fp8 calls, by full rounds, remainder and depth: taken where it gains on
-# every box that timed it, else one launch
+# the mean of the cards that timed it, else one launch
 @pytest.mark.parametrize("rounds,K,strip", [
     ((3, 8), 4096, True), ((3, 8), 8192, True), ((3, 8), 3072, False), ((3, 8), 512, False),
     ((3, 4), 4096, True), ((3, 4), 2048, True), ((3, 4), 1024, False), ((3, 4), 256, False),
